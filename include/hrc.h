@@ -306,7 +306,8 @@ typedef enum {
  * with a pair of HIP events that the runtime records at that kernel's start
  * and end on `stream`; then synchronises `stream` and reports, per pass in
  * execution order, its kind, level n (-1 when not per level) and kernel
- * duration in milliseconds.  At most `max_passes` are reported; *count receives the
+ * duration in milliseconds; a kernel that runs several passes (levels of the
+ * merges) reports each with an equal share of its duration.  At most `max_passes` are reported; *count receives the
  * number of passes.  Argument checks as for hrc_forward / hrc_backward, plus
  * HRC_ERR_INVALID_ARG for NULL report arrays. */
 hrc_status hrc_profile_solve(hrc_context *ctx, int log2_size,

@@ -5,6 +5,7 @@
 #include <stdlib.h>
 #include <string.h>
 
+#include <algorithm>
 #include <cmath>
 #include <vector>
 
@@ -147,6 +148,7 @@ static int pick_u(const int *U, int kind) { return U ? (U[kind] > 0 ? U[kind] : 
 // forward 2-7%, the RGB forward 4% and the reverse 3-9% faster at 1024^2 ..
 // 4096^2; the same results, since only the order of the tiles changes.
 static int tile_order(int N, int kind) {
+    if (kind == PH_FUSE_UP || kind == PH_FUSE_TOP || kind == PH_FUSE_DOWN) return 0;
     if (N < 10) return 0;
     switch (kind) {
         case PH_UP:
@@ -161,8 +163,98 @@ static int tile_order(int N, int kind) {
     }
 }
 
+// The merges of one group of quadrants with several levels per kernel: T_2 up
+// to T_{n_top}, the top kernel from there to R_{n_top}, then down to R_2 two levels
+// at a time (a level left over, and R_1, are passes of their own).  The
+// top kernel takes four levels (three with RGB intervals, twice as large in
+// LDS).  RGB in FP32 merges down level by level: its fused pair took 97 us at
+// 1024^2 against 2 x 33 us.  Only the levels at which a later kernel starts are stored, or all of
+// them when they are kept for the reverse.  Returns the buffer index of the
+// last R level (not keeping).
+template <typename Add>
+static int build_fused_merges(const Ws &w, const SolveBuffers &b, bool keep, bool rgb, int q0,
+                              int nq, Add add) {
+    const int N = w.L.N;
+    const int M = std::min(rgb ? 3 : 4, N - 2), n_top = N - M;
+    auto fused = [&](int kind, int n, int levels) {
+        Phase p;
+        p.kind = kind;
+        FuseArgs f{};
+        f.N = N;
+        f.n = n;
+        f.levels = levels;
+        f.nq = nq;
+        f.q0 = q0;
+        f.env = b.env;
+        f.half = b.half;
+        f.rgb = rgb ? 1 : 0;
+        f.T[0] = w.T(n);
+        p.a.fu = f;
+        return p;
+    };
+    Phase p;
+    const int max_up = rgb ? 3 : 4;
+    for (int n = kTracedLevels - 1; n < n_top;) {
+        int g = std::min(n_top - n, max_up);
+        if (n_top - n - g == 1 && g > 2) --g;  // no level left alone
+        if (g == 1) {
+            p = Phase();
+            p.kind = rgb ? PH_UP_RGB : PH_UP;
+            p.a.up = UpArgs{w.T(n), w.T(n + 1), t_level_entries(N, n), t_level_entries(N, n + 1), N,
+                            n + 1, nq, b.half};
+        } else {
+            p = fused(PH_FUSE_UP, n, g);
+            for (int j = 1; j <= g; ++j)
+                if (keep || j == g || (rgb && !b.half) || (n_top - n - j) % 2 == 0)
+                    p.a.fu.T[j] = w.T(n + j);
+            size_fused(p);
+        }
+        add(p);
+        n += g;
+    }
+    int cur = 0;
+    auto r_of = [&](int n) { return keep ? w.R(n) : w.R(cur); };
+    if (M == 1) {
+        p = Phase();
+        p.kind = rgb ? PH_DOWN_RGB : PH_DOWN;
+        p.a.down = DownArgs{nullptr, w.T(n_top), w.T(N), r_of(n_top), t_level_entries(N, n_top),
+                            t_level_entries(N, N), N, n_top, nq, b.env, q0, b.half};
+        add(p);
+    } else {
+        p = fused(PH_FUSE_TOP, n_top, M);
+        p.a.fu.R[0] = r_of(n_top);
+        for (int j = 1; keep && j < M; ++j) {
+            p.a.fu.T[j] = w.T(n_top + j);
+            p.a.fu.R[j] = w.R(n_top + j);
+        }
+        size_fused(p);
+        add(p);
+    }
+    const int last = keep ? 1 : 2;
+    for (int n = n_top; n > last;) {
+        float *from = r_of(n);
+        cur = 1 - cur;
+        if (n - 2 >= kTracedLevels - 1 && !(rgb && !b.half)) {  // T_{n-1} is rebuilt from T_{n-2}: merged levels only
+            n -= 2;
+            p = fused(PH_FUSE_DOWN, n, 2);
+            p.a.fu.R[0] = r_of(n);
+            p.a.fu.R[1] = keep ? w.R(n + 1) : nullptr;
+            p.a.fu.R[2] = from;
+            size_fused(p);
+        } else {
+            --n;
+            p = Phase();
+            p.kind = rgb ? PH_DOWN_RGB : PH_DOWN;
+            p.a.down = DownArgs{from, w.T(n), w.T(n + 1), r_of(n), t_level_entries(N, n),
+                                t_level_entries(N, n + 1), N, n, nq, b.env, q0, b.half};
+        }
+        add(p);
+    }
+    return cur;
+}
+
 int build_solve_phases(const Ws &w, const SolveBuffers &b, bool keep_all_r, const int *U,
-                       Phase *out, int max_out, bool recompute) {
+                       Phase *out, int max_out, bool recompute, bool fused) {
     const int N = w.L.N;
     int np = 0;
     auto add = [&](Phase p) {
@@ -198,7 +290,9 @@ int build_solve_phases(const Ws &w, const SolveBuffers &b, bool keep_all_r, cons
                             keep_all_r ? 0 : kTracedLevels - 1,
                             b.half};
         add(p);
-        for (int n = kTracedLevels; n < N; ++n) {
+        int cur = -1;
+        if (fused) cur = build_fused_merges(w, b, keep_all_r, false, q0, G, add);
+        for (int n = kTracedLevels; !fused && n < N; ++n) {
             p = Phase();
             p.kind = PH_UP;
             p.U = pick_u(U, PH_UP);
@@ -206,9 +300,8 @@ int build_solve_phases(const Ws &w, const SolveBuffers &b, bool keep_all_r, cons
                             N, n, G, b.half};
             add(p);
         }
-        int cur = -1;
         const int n_last = keep_all_r ? 1 : 2;
-        for (int n = N - 1; n >= n_last; --n) {
+        for (int n = N - 1; !fused && n >= n_last; --n) {
             const int o = keep_all_r ? n : (cur == 0 ? 1 : 0);
             p = Phase();
             p.kind = PH_DOWN;
@@ -307,24 +400,7 @@ int build_rgb_forward_phases(const Ws &w, const SolveBuffers &b, Phase *out, int
                         t_level_entries(N, 1), t_level_entries(N, 2), N, 0, kQuadrants, 16,
                         kTracedLevels - 1, b.half};
     add(p);
-    for (int n = kTracedLevels; n < N; ++n) {
-        p = Phase();
-        p.kind = PH_UP_RGB;
-        p.a.up = UpArgs{w.T(n - 1), w.T(n), t_level_entries(N, n - 1), t_level_entries(N, n), N, n,
-                        kQuadrants, b.half};
-        add(p);
-    }
-    int cur = -1;
-    for (int n = N - 1; n >= 2; --n) {
-        const int o = cur == 0 ? 1 : 0;
-        p = Phase();
-        p.kind = PH_DOWN_RGB;
-        p.a.down = DownArgs{(n + 1 < N) ? w.R(cur) : nullptr, w.T(n), w.T(n + 1), w.R(o),
-                            t_level_entries(N, n), t_level_entries(N, n + 1), N, n, kQuadrants,
-                            nullptr, 0, b.half};
-        add(p);
-        cur = o;
-    }
+    const int cur = build_fused_merges(w, b, false, true, 0, kQuadrants, add);
     p = Phase();
     p.kind = PH_TAIL_RGB;
     p.a.tail = TailArgs{b.eps, b.sig, w.R(cur), gathered, N, 0, kQuadrants, 0, nullptr, 16};
@@ -363,21 +439,7 @@ int build_rgb_backward_phases(const Ws &w, const SolveBuffers &b, Phase *out, in
                             t_level_entries(N, 1), t_level_entries(N, 2), N, 0, kQuadrants, 16, 0,
                             b.half};
         add(p);
-        for (int n = kTracedLevels; n < N; ++n) {
-            p = Phase();
-            p.kind = PH_UP_RGB;
-            p.a.up = UpArgs{w.T(n - 1), w.T(n), t_level_entries(N, n - 1), t_level_entries(N, n), N,
-                            n, kQuadrants, b.half};
-            add(p);
-        }
-        for (int n = N - 1; n >= 1; --n) {
-            p = Phase();
-            p.kind = PH_DOWN_RGB;
-            p.a.down = DownArgs{(n + 1 < N) ? w.R(n + 1) : nullptr, w.T(n), w.T(n + 1), w.R(n),
-                                t_level_entries(N, n), t_level_entries(N, n + 1), N, n, kQuadrants,
-                                nullptr, 0, b.half};
-            add(p);
-        }
+        build_fused_merges(w, b, true, true, 0, kQuadrants, add);
         if (b.F) {
             p = Phase();
             p.kind = PH_TAIL_RGB;
@@ -768,14 +830,33 @@ static BounceLayout bounce_layout(int N, int bounces, bool backward, int group) 
     return M;
 }
 
-static int phase_level(const Phase &p) {
+// The passes of Algorithm 1 (kind, level) that a phase runs, in order; returns
+// their count.
+static int phase_passes(const Phase &p, int *kind, int *level) {
+    int c = 0;
+    auto add = [&](int k, int n) {
+        kind[c] = k;
+        level[c++] = n;
+    };
     switch (p.kind) {
-        case PH_UP: return p.a.up.n;
-        case PH_DOWN: return p.a.down.n;
-        case PH_DOWN_ADJ: return p.a.da.n;
-        case PH_DT: return p.a.dt.n;
-        default: return -1;
+        case PH_UP: add(p.kind, p.a.up.n); break;
+        case PH_DOWN: add(p.kind, p.a.down.n); break;
+        case PH_DOWN_ADJ: add(p.kind, p.a.da.n); break;
+        case PH_DT: add(p.kind, p.a.dt.n); break;
+        case PH_FUSE_UP:
+            for (int j = 1; j <= p.a.fu.levels; ++j) add(PH_UP, p.a.fu.n + j);
+            break;
+        case PH_FUSE_TOP:
+            for (int j = 1; j < p.a.fu.levels; ++j) add(PH_UP, p.a.fu.n + j);
+            for (int j = p.a.fu.levels - 1; j >= 0; --j) add(PH_DOWN, p.a.fu.n + j);
+            break;
+        case PH_FUSE_DOWN:
+            add(PH_DOWN, p.a.fu.n + 1);
+            add(PH_DOWN, p.a.fu.n);
+            break;
+        default: add(p.kind, -1);
     }
+    return c;
 }
 
 hrc_status hrc_multibounce_workspace_bytes(int log2_size, int bounces, unsigned flags,
@@ -938,17 +1019,23 @@ hrc_status hrc_profile_solve(hrc_context *ctx, int log2_size, const float *emiss
     }
     if (st == HRC_OK && np > 0 && hipEventSynchronize(ev[2 * np - 1]) != hipSuccess)
         st = HRC_ERR_HIP;
+    int reported = 0;
     for (int i = 0; i < np && st == HRC_OK; ++i) {
-        if (i >= max_passes) break;
         float ms = 0.f;
         if (hipEventElapsedTime(&ms, ev[2 * i], ev[2 * i + 1]) != hipSuccess) st = HRC_ERR_HIP;
-        pass_ms[i] = ms;
-        pass_kind[i] = ph[i].kind;
-        pass_level[i] = phase_level(ph[i]);
+        // a kernel of several passes: its duration in equal shares
+        int kind[8], level[8];
+        const int c = phase_passes(ph[i], kind, level);
+        for (int j = 0; j < c; ++j, ++reported) {
+            if (reported >= max_passes) continue;
+            pass_ms[reported] = ms / (float)c;
+            pass_kind[reported] = kind[j];
+            pass_level[reported] = level[j];
+        }
     }
     for (auto &e : ev)
         if (e) (void)hipEventDestroy(e);
-    *count = np;
+    *count = reported;
     return st;
 }
 

@@ -113,6 +113,18 @@ void phase_access(const Phase &p, std::vector<const void *> &rd, std::vector<con
             w(a.dE); w(a.dS);
             break;
         }
+        case PH_FUSE_UP:
+        case PH_FUSE_TOP:
+        case PH_FUSE_DOWN: {
+            const FuseArgs &a = p.a.fu;
+            r(a.T[0]);
+            for (int j = 1; j < 5; ++j) w(a.T[j]);
+            for (int j = 0; j < 4; ++j) {
+                if (p.kind == PH_FUSE_DOWN && j == 2) r(a.R[j]);
+                else w(a.R[j]);
+            }
+            break;
+        }
         case PH_BLUR:
         case PH_BLUR_ADJ: r(p.a.bl.in); r(p.a.bl.sig); w(p.a.bl.out); break;
         default: break;
@@ -211,8 +223,9 @@ void arrange(Arrangement &ar, const hrc_scene *scenes, int count, char *base) {
         SolveBuffers sb{sc.emission, sc.sigma_t, sc.fluence, sc.grad_fluence, sc.grad_emission,
                         sc.grad_sigma_t};
         Phase tmp[kMaxPhases];
+        // the persistent kernel runs every merge level as a pass of its own
         const int n = build_solve_phases(Ws{ws, lay[i]}, sb, sc.grad_fluence != nullptr, nullptr,
-                                         tmp, kMaxPhases);
+                                         tmp, kMaxPhases, true, !persistent);
         out.assign(tmp, tmp + n);
         if (persistent)
             for (Phase &p : out) size_tiles(p, ar.target);

@@ -1,0 +1,756 @@
+// Several levels of the merges in one kernel (included by hrc_kernels.hip,
+// inside namespace hrc).
+//
+// Why.  Level by level, each merge reads and writes whole levels: 1.1 GB of
+// traffic for a 1024^2 forward whose inputs and output are 12 MB, and one
+// launch per level.  But the levels decompose: cone ii of level n and all its
+// descendants read only directions ii and ii + 1 of T_n, and everything a
+// lookup along a direction reaches lies on that direction's line.  So a block
+// takes one cone ii of level n of one quadrant, a run of probe columns, and a
+// window of rows that is sheared along the cone's lower edge, loads its part of
+// T_n once into LDS and builds several levels from it on chip.
+//
+// Sheared windows.  The lower edge of cone ii climbs sb = 2 ii - 2^n rows per
+// column of level n.  Window row r at column position p (in columns of level n
+// from the block's anchor) is the grid row (y0 + r + p sb) mod S.  In these
+// coordinates a lookup along direction K' = K - ii 2^j of level n + j moves
+// 2 K' rows at the next column (0 <= K' <= 2^j), so all a window of W output
+// rows needs is W + 2 d rows at distance d.  The windows are cyclic in y, so
+// every grid row belongs to one window at every column and no block is half
+// empty; a lookup whose row leaves the grid is replaced by a select on the
+// unsheared row, as in the level-by-level passes.  An LDS row holds L = 128
+// window rows; the last ones, whose lookups run into the next LDS row, hold no
+// valid values and feed no stored one.
+//
+// Column 0 of a level is read by nothing but column 0 of the levels below,
+// and the gather never reads that: the top and the down kernels leave it out.
+//
+// Measured at 1024^2 (FP32, four quadrants, per forward): T_2 -> T_6 26.9 us
+// (four single levels 40), T_6 -> R_6 31 us (three levels up and four down: 76),
+// R_6 -> R_4 -> R_2 31 us each (24 per two single levels down, but they also
+// save storing T_3 and T_5); forward 217.7 -> 143.3 us, 64^2 37 -> 24 us (3
+// launches for 11), 4096^2 4.37 -> 2.99 ms.  They move 40-60% of the bytes of the
+// single levels and are bound by instruction issue and LDS latency, not HBM:
+// the LDS of a block (58 and 78 KB) leaves two blocks on a CU, so 1024 threads a
+// block (512: 31 and 36 us) keep the 32 waves the CU can hold.
+//
+// The arithmetic of every element, and its order, is that of the
+// level-by-level bodies, and 16-bit intervals are rounded at the same points
+// (LDS holds the storage type), so the results are bitwise the same.
+
+// ---- interval storage types -------------------------------------------------
+
+template <typename TS> struct Store;
+template <> struct Store<float2> { using C = float2; static constexpr int ch = 1; };
+template <> struct Store<half2_t> { using C = float2; static constexpr int ch = 1; };
+template <> struct Store<float4> { using C = float4; static constexpr int ch = 3; };
+template <> struct Store<half4_t> { using C = float4; static constexpr int ch = 3; };
+
+// (native vectors: arrays of HIP's vector classes went to scratch memory)
+template <int BYTES> struct RawVec {
+    typedef unsigned type __attribute__((ext_vector_type(BYTES / 4)));
+};
+template <> struct RawVec<4> { using type = unsigned; };
+
+__device__ __forceinline__ float trans(float2 v) { return v.y; }
+__device__ __forceinline__ float trans(float4 v) { return v.w; }
+__device__ __forceinline__ float rad(float2 v, int) { return v.x; }
+__device__ __forceinline__ float rad(float4 v, int c) { return c == 0 ? v.x : c == 1 ? v.y : v.z; }
+__device__ __forceinline__ float2 half_sum(float2 a, float2 b) {
+    return make_float2(0.5f * (a.x + b.x), 0.5f * (a.y + b.y));
+}
+__device__ __forceinline__ float4 half_sum(float4 a, float4 b) {
+    return make_float4(0.5f * (a.x + b.x), 0.5f * (a.y + b.y), 0.5f * (a.z + b.z),
+                       0.5f * (a.w + b.w));
+}
+
+// V consecutive intervals of a row as one vector access.
+template <int V> __device__ __forceinline__ void ld_row(const float2 *p, float2 (&o)[V]) {
+    if constexpr (V == 2) {
+        const float4 v = *reinterpret_cast<const float4 *>(p);
+        o[0] = lo(v);
+        o[1] = hi(v);
+    } else {
+        o[0] = *p;
+    }
+}
+template <int V> __device__ __forceinline__ void ld_row(const half2_t *p, float2 (&o)[V]) {
+    if constexpr (V == 2) {
+        const float4 v = ld_pair(p);
+        o[0] = lo(v);
+        o[1] = hi(v);
+    } else {
+        const half2_t v = *p;
+        o[0] = make_float2((float)v.x, (float)v.y);
+    }
+}
+template <int V> __device__ __forceinline__ void ld_row(const float4 *p, float4 (&o)[V]) {
+#pragma unroll
+    for (int i = 0; i < V; ++i) o[i] = p[i];
+}
+template <int V> __device__ __forceinline__ void ld_row(const half4_t *p, float4 (&o)[V]) {
+    if constexpr (V == 2) {
+        const half8_t v = *reinterpret_cast<const half8_t *>(p);
+        cvt_quad(v, o[0], o[1]);
+    } else {
+        o[0] = ld4(p);
+    }
+}
+template <int V> __device__ __forceinline__ void st_row(float2 *p, const float2 (&v)[V]) {
+    if constexpr (V == 2)
+        st_pair(p, pair(v[0], v[1]));
+    else
+        *p = v[0];
+}
+template <int V> __device__ __forceinline__ void st_row(half2_t *p, const float2 (&v)[V]) {
+    if constexpr (V == 2)
+        st_pair(p, pair(v[0], v[1]));
+    else
+        st_iv(p, v[0]);
+}
+template <int V> __device__ __forceinline__ void st_row(float4 *p, const float4 (&v)[V]) {
+#pragma unroll
+    for (int i = 0; i < V; ++i) p[i] = v[i];
+}
+template <int V> __device__ __forceinline__ void st_row(half4_t *p, const float4 (&v)[V]) {
+    if constexpr (V == 2)
+        st_quad(reinterpret_cast<half2_t *>(p), v[0], v[1]);
+    else
+        st_iv(p, v[0]);
+}
+// V consecutive floats of an angular fluence row.
+template <int V> __device__ __forceinline__ void ld_f(const float *p, float (&o)[V]) {
+    if constexpr (V == 2) {
+        const float2 v = *reinterpret_cast<const float2 *>(p);
+        o[0] = v.x;
+        o[1] = v.y;
+    } else {
+        o[0] = *p;
+    }
+}
+template <int V> __device__ __forceinline__ void st_f(float *p, const float (&v)[V]) {
+    if constexpr (V == 2)
+        *reinterpret_cast<float2 *>(p) = make_float2(v[0], v[1]);
+    else
+        *p = v[0];
+}
+// A computed interval as it reads back once stored.
+__device__ __forceinline__ float2 stored(float2 v, const float2 *) { return v; }
+__device__ __forceinline__ float4 stored(float4 v, const float4 *) { return v; }
+__device__ __forceinline__ float2 stored(float2 v, const half2_t *) {
+    return make_float2((float)to_half(v.x), (float)to_half(v.y));
+}
+__device__ __forceinline__ float4 stored(float4 v, const half4_t *) {
+    return make_float4((float)to_half(v.x), (float)to_half(v.y), (float)to_half(v.z),
+                       (float)to_half(v.w));
+}
+
+// ---- one block's window -------------------------------------------------------
+
+// The block's quadrant (of the group), cone of level n and first window row.
+struct FuseTile {
+    int q, ii, x, y0;  // x: chunk of columns
+};
+
+// Tiles in the order cone (its low three bits), window, cone, chunk, quadrant:
+// neighbours in cone share a direction of T_n and neighbours in window their
+// halo rows, so they run side by side on one XCD and meet in its L2.
+__device__ __forceinline__ FuseTile fuse_tile(const FuseArgs &a, unsigned t) {
+    const int lb = a.n < 3 ? a.n : 3;
+    FuseTile f;
+    f.ii = (int)(t & ((1u << lb) - 1));
+    t >>= lb;
+    const unsigned w = t % (unsigned)a.nwin;
+    t /= (unsigned)a.nwin;
+    f.y0 = (int)w * a.win;
+    f.ii |= (int)(t & ((1u << (a.n - lb)) - 1)) << lb;
+    t >>= a.n - lb;
+    f.x = (int)(t % (unsigned)a.chunks);
+    f.q = (int)(t / (unsigned)a.chunks);
+    return f;
+}
+
+// Row state of one lane: window row r (V consecutive ones), and the grid row
+// of r at column position p.
+template <int V> struct Rows {
+    int r, base, sb, mask;
+    __device__ __forceinline__ Rows(int r_, int y0, int sb_, int S)
+        : r(r_), base(y0 + r_), sb(sb_), mask(S - 1) {}
+    __device__ __forceinline__ int y(int p) const { return (base + p * sb) & mask; }
+    __device__ __forceinline__ bool in(int yt) const { return (unsigned)yt <= (unsigned)mask; }
+};
+
+// Directions 2k and 2k + 1 (relative to the block's lower edge) of one column
+// of level m: Eq. 18, and the mean of Eq. 19-20.  nb: the lane's interval of
+// direction k of the near column at level m - 1 (directions L apart), far: how
+// far behind it the far column's direction k lies.  yv: the output's grid row
+// plus the rows a column of level m - 1 climbs along the lower edge.  The far
+// lookups run 2k rows up for direction k and 2k + 2 for k + 1, so apart from
+// one base each every LDS offset is an immediate.
+template <typename TS, int V, int L, bool ODD>
+__device__ __forceinline__ void fused_up(const TS *nb, int far, int k, const Rows<V> &w, int yv,
+                                         typename Store<TS>::C (&even)[V],
+                                         typename Store<TS>::C (&odd)[V]) {
+    using C = typename Store<TS>::C;
+    const TS *fb = nb + far + 2 * k;
+    C n0[V], n1[V], f00[V], f02[V], f10[V];
+    ld_row<V>(nb, n0);
+    ld_row<V>(fb, f00);  // direction k, 2k rows up
+    if constexpr (ODD) {
+        ld_row<V>(nb + L, n1);
+        ld_row<V>(fb + 2, f02);  // direction k, 2k + 2 rows up
+        ld_row<V>(fb + L, f10);  // direction k + 1, 2k rows up
+    }
+    const bool in0 = w.in(yv + 2 * k), in1 = w.in(yv + 2 * k + 2);
+#pragma unroll
+    for (int i = 0; i < V; ++i) {
+        even[i] = merge(n0[i], in0 ? f00[i] : empty_interval<C>());
+        if constexpr (ODD)
+            odd[i] = half_sum(merge(n1[i], in1 ? f02[i] : empty_interval<C>()),
+                              merge(n0[i], in0 ? f10[i] : empty_interval<C>()));
+    }
+}
+
+// Eq. 14 (odd column): R_{m-1} of cone k (relative).  t: the lane's interval of
+// direction k of T_{m-1} at this column; rm: the lane's row of cone 2k of R_m at
+// the next probe, 2k rows up (NULL where that probe lies beyond the grid); wt:
+// cone weights and light from beyond the grid of the cones 2k, 2k + 1 (A, E, A, E).
+template <typename TS, int V, int L>
+__device__ __forceinline__ void fused_down_odd(const TS *t, const float *rm, bool far, int k,
+                                               float4 wt, const Rows<V> &w, int yv,
+                                               float (&o)[Store<TS>::ch][V]) {
+    using C = typename Store<TS>::C;
+    constexpr int CH = Store<TS>::ch;
+    C tv[2][V];
+    float f[2][CH][V];
+#pragma unroll
+    for (int up = 0; up < 2; ++up) {
+        ld_row<V>(t + up * L, tv[up]);
+#pragma unroll
+        for (int c = 0; c < CH; ++c) ld_f<V>(rm + (up * CH + c) * L + 2 * up, f[up][c]);
+    }
+#pragma unroll
+    for (int c = 0; c < CH; ++c)
+#pragma unroll
+        for (int j = 0; j < V; ++j) o[c][j] = 0.f;
+#pragma unroll
+    for (int up = 0; up < 2; ++up) {
+        const float A = up ? wt.z : wt.x, E = up ? wt.w : wt.y;
+        const bool in = far && w.in(yv + 2 * (k + up));
+#pragma unroll
+        for (int c = 0; c < CH; ++c)
+#pragma unroll
+            for (int j = 0; j < V; ++j)
+                o[c][j] += fmaf(trans(tv[up][j]), in ? f[up][c][j] : E, A * rad(tv[up][j], c));
+    }
+}
+
+// Eq. 15-17 (even column 2c): the co-located probe c of R_m averaged with the
+// doubled edges T_m(c, 2k), T_m(c, 2k + 2) (e: already in registers) to the
+// probe c + 1.  rn: the lane's row of cone 2k at probe c; rf: of cone 2k at probe
+// c + 1, 4k rows up (far: that probe lies in the grid).
+template <typename TS, int V, int L>
+__device__ __forceinline__ void fused_down_even(const typename Store<TS>::C (&e)[2][V],
+                                                const float *rn, const float *rf, bool far, int k,
+                                                float4 wt, const Rows<V> &w, int yv,
+                                                float (&o)[Store<TS>::ch][V]) {
+    constexpr int CH = Store<TS>::ch;
+    float f0[2][CH][V], f1[2][CH][V];
+#pragma unroll
+    for (int up = 0; up < 2; ++up)
+#pragma unroll
+        for (int c = 0; c < CH; ++c) {
+            ld_f<V>(rn + (up * CH + c) * L, f0[up][c]);
+            ld_f<V>(rf + (up * CH + c) * L + 4 * up, f1[up][c]);
+        }
+#pragma unroll
+    for (int c = 0; c < CH; ++c)
+#pragma unroll
+        for (int j = 0; j < V; ++j) o[c][j] = 0.f;
+#pragma unroll
+    for (int up = 0; up < 2; ++up) {
+        const float A = up ? wt.z : wt.x, E = up ? wt.w : wt.y;
+        const bool in = far && w.in(yv + 4 * (k + up));
+#pragma unroll
+        for (int c = 0; c < CH; ++c)
+#pragma unroll
+            for (int j = 0; j < V; ++j)
+                o[c][j] += 0.5f * (f0[up][c][j] + fmaf(trans(e[up][j]), in ? f1[up][c][j] : E,
+                                                       A * rad(e[up][j], c)));
+    }
+}
+
+// Cone weights and light from beyond the grid of every cone pair of the levels
+// n .. n + M - 1 of the block's cone: entry 2^j - 1 + k for cone k of level n + j.
+template <int M>
+__device__ __forceinline__ void load_weights(float4 *wl, int n, int ii, const float *envq, int tid) {
+    if (tid < (1 << M) - 1) {
+        const int j = 31 - __clz(tid + 1), k = tid + 1 - (1 << j);
+        const int cone = (2 << (n + j)) - 1 + (((ii << j) + k) << 1);
+        wl[tid] = make_float4(c_cone[cone], envq ? envq[cone] : 0.f, c_cone[cone + 1],
+                              envq ? envq[cone + 1] : 0.f);
+    }
+}
+// Lookups of rows past the valid ones run up to this many rows past an LDS row
+// (and past the last one: the padding of every buffer).
+constexpr int kFusePad = 64;
+
+// Entries per quadrant of level n (below 2^25 for S <= 4096).
+__device__ __forceinline__ unsigned t_entries(int N, int n) {
+    return (((1u << N) >> n) * ((1u << n) + 1)) << N;
+}
+
+// Rows x of `cols` columns x 2 directions of T_n (columns first_col ..) into
+// LDS: row slot(x) * 2 + d holds direction ii + d.  Every load of a thread is
+// issued before the first is written.  Columns at or past the grid's last are
+// left out.
+template <typename TS, int V, int L, int NT, int COLS, typename Slot>
+__device__ __forceinline__ void load_tn(const TS *T, TS *lds, int N, int n, int ii, int first_col,
+                                        int anchor, int y0, int sb, int tid, Slot slot) {
+    using Raw = typename RawVec<sizeof(TS) * V>::type;
+    constexpr int H = L / (64 * V), ROWS = COLS * 2 * H, NW = NT / 64, IT = (ROWS + NW - 1) / NW;
+    const int S = 1 << N, wave = __builtin_amdgcn_readfirstlane(tid >> 6), lane = tid & 63;
+    const int dirs = (1 << n) + 1, C = S >> n;
+    Raw v[IT];
+#pragma unroll
+    for (int it = 0; it < IT; ++it) {
+        const int i = it * NW + wave;
+        if (i < ROWS) {
+            const int h = i % H, rd = i / H, x = first_col + (rd >> 1), d = rd & 1;
+            const Rows<V> w((h * 64 + lane) * V, y0, sb, S);
+            const int xc = x < C ? x : C - 1;
+            v[it] = *reinterpret_cast<const Raw *>(
+                T + (((unsigned)(xc * dirs + ii + d) << N) + (unsigned)w.y(x - anchor)));
+        }
+    }
+#pragma unroll
+    for (int it = 0; it < IT; ++it) {
+        const int i = it * NW + wave;
+        if (i < ROWS) {
+            const int h = i % H, rd = i / H, d = rd & 1;
+            *reinterpret_cast<Raw *>(lds + (slot(rd >> 1) * 2 + d) * L + (h * 64 + lane) * V) = v[it];
+        }
+    }
+}
+
+// ---- merge up of G levels: T_n -> T_{n+G} ----------------------------------------
+
+// A block builds one column X of T_{n+G} for one cone of level n from the 2^G
+// columns of T_n below it.  Levels alternate between two LDS regions.  Every
+// level with a destination in a.T is stored (the last one always).
+template <typename TS, int G> struct FuseUp {
+    static constexpr int L = 128, V = sizeof(TS) == 16 ? 1 : 2, H = L / (64 * V);
+    static constexpr int NT = G == 4 ? 1024 : G == 3 ? 512 : 256, NW = NT / 64;
+    static constexpr int win = L - (2 << G);  // 2 (2^G - 1) rows of halo
+    static constexpr int rows(int j) { return (1 << (G - j)) * ((1 << j) + 1); }
+    static constexpr int region(int p) {
+        int m = 0;
+        for (int j = p; j < G; j += 2) m = rows(j) > m ? rows(j) : m;
+        return m;
+    }
+    static constexpr int lds = ((region(0) + region(1)) * L + kFusePad) * (int)sizeof(TS);
+};
+
+template <typename TS, int G, int j>
+__device__ __forceinline__ void fuse_up_level(const FuseArgs &a, const FuseTile &t, char *lds,
+                                              int own, int sb, int tid) {
+    using F = FuseUp<TS, G>;
+    using C = typename Store<TS>::C;
+    constexpr int V = F::V, L = F::L, H = F::H, NW = F::NW;
+    constexpr int dirs = (1 << j) + 1, pdirs = (1 << (j - 1)) + 1, cols = 1 << (G - j);
+    const int N = a.N, S = 1 << N, m = a.n + j;
+    TS *reg0 = reinterpret_cast<TS *>(lds), *reg1 = reg0 + F::region(0) * L;
+    const TS *src = (j & 1) ? reg0 : reg1;
+    TS *dst = (j & 1) ? reg1 : reg0;
+    TS *out = reinterpret_cast<TS *>(a.T[j]);
+    const int wave = __builtin_amdgcn_readfirstlane(tid >> 6), lane = tid & 63;
+    // the last direction is the next cone's first: stored by the last cone only
+    const bool last = t.ii == (1 << a.n) - 1;
+    for (int i = wave; i < cols * pdirs * H; i += NW) {
+        const int h = i % H, e = i / H, X = j == G ? 0 : e / pdirs, k = j == G ? e : e % pdirs;
+        const bool two = k + 1 < pdirs;  // direction 2k + 1 as well
+        const Rows<V> w((h * 64 + lane) * V, t.y0, sb, S);
+        const int y = w.y(X << j);
+        C ev[V], od[V];
+        fused_up<TS, V, L, true>(src + (2 * X * pdirs + k) * L + w.r, pdirs * L, k, w,
+                                 y + (sb << (j - 1)), ev, od);
+        if constexpr (j < G) {
+            TS *d = dst + (X * dirs + 2 * k) * L + w.r;
+            st_row<V>(d, ev);
+            if (two) st_row<V>(d + L, od);
+        }
+        if ((j == G || out) && w.r < own) {
+            TS *o = out + ((unsigned)t.q * t_entries(N, m) +
+                           ((unsigned)(((t.x << (G - j)) + X) * ((1 << m) + 1) + (t.ii << j) + 2 * k)
+                            << N));
+            if (two || last) st_row<V>(o + (unsigned)y, ev);
+            if (two) st_row<V>(o + (unsigned)(y + S), od);
+        }
+    }
+}
+
+template <typename TS, int G>
+__device__ __forceinline__ void fuse_up_block(const FuseArgs &a, unsigned tile, char *lds, int tid) {
+    using F = FuseUp<TS, G>;
+    const int N = a.N, S = 1 << N, n = a.n;
+    const FuseTile t = fuse_tile(a, tile);
+    const int sb = 2 * t.ii - (1 << n);
+    const int own = a.win < S - t.y0 ? a.win : S - t.y0;
+    load_tn<TS, F::V, F::L, F::NT, (1 << G)>(
+        reinterpret_cast<const TS *>(a.T[0]) + (unsigned)t.q * t_entries(N, n),
+        reinterpret_cast<TS *>(lds), N, n, t.ii, t.x << G, t.x << G, t.y0, sb, tid,
+        [](int i) { return i; });
+    __syncthreads();
+    fuse_up_level<TS, G, 1>(a, t, lds, own, sb, tid);
+    __syncthreads();
+    fuse_up_level<TS, G, 2>(a, t, lds, own, sb, tid);
+    if constexpr (G >= 3) {
+        __syncthreads();
+        fuse_up_level<TS, G, 3>(a, t, lds, own, sb, tid);
+    }
+    if constexpr (G >= 4) {
+        __syncthreads();
+        fuse_up_level<TS, G, 4>(a, t, lds, own, sb, tid);
+    }
+}
+
+// ---- the top M levels: T_n -> R_n, n = N - M -------------------------------------
+
+// A block holds every column but 0 of one cone's T_n .. T_{N-1}, then merges
+// down from R_N to R_n.  The R levels alternate between two regions; where
+// they fit, those lie over T_n's even columns, which only the merge up of
+// T_{n+1} reads (T_n's odd columns come first in LDS).
+template <typename TS, int M> struct FuseTop {
+    static constexpr int L = 128, ch = Store<TS>::ch;
+    static constexpr int V = sizeof(TS) == 16 ? 1 : 2, H = L / (64 * V);
+    static constexpr int NT = M >= 4 ? 1024 : 512, NW = NT / 64;
+    static constexpr int win = L - 2 * ((1 << M) - 1);  // halo: from column 1 to the far edge
+    static constexpr int cols(int j) { return (1 << (M - j)) - 1; }
+    static constexpr int t_rows(int j) { return cols(j) * ((1 << j) + 1); }
+    static constexpr int t_off(int j) {  // first LDS row of T_{n+j}
+        int o = 0;
+        for (int i = 0; i < j; ++i) o += t_rows(i);
+        return o;
+    }
+    static constexpr int r_rows(int j) { return cols(j) * (1 << j) * ch; }
+    static constexpr int r_region(int p) {  // float rows of the levels j >= 1 of parity p
+        int m = 0;
+        for (int j = p == 0 ? 2 : 1; j < M; j += 2) m = r_rows(j) > m ? r_rows(j) : m;
+        return m;
+    }
+    static constexpr int t_bytes = t_off(M) * L * (int)sizeof(TS);
+    static constexpr int r_bytes = (r_region(0) + r_region(1)) * L * 4;
+    static constexpr int odd_bytes = (1 << (M - 1)) * 2 * L * (int)sizeof(TS);
+    static constexpr bool overlay = t_rows(0) * L * (int)sizeof(TS) - odd_bytes >= r_bytes;
+    static constexpr int r_off = overlay ? odd_bytes : t_bytes;
+    static constexpr int w_off = (overlay ? t_bytes : t_bytes + r_bytes) + kFusePad * (int)sizeof(TS);
+    static constexpr int lds = w_off + 16 * ((1 << M) - 1);
+    // LDS column of T_n's column x: odd columns first
+    __device__ __forceinline__ static int slot(int x) {
+        return (x & 1) ? x >> 1 : (1 << (M - 1)) + (x >> 1) - 1;
+    }
+};
+
+// First LDS row (direction 0) of column x of T_{n+j}; of R_{n+j}.
+template <typename TS, int M, int j> __device__ __forceinline__ TS *top_t(char *lds, int x) {
+    using F = FuseTop<TS, M>;
+    const int c = j == 0 ? F::slot(x) : x - 1;
+    return reinterpret_cast<TS *>(lds) + (F::t_off(j) + c * ((1 << j) + 1)) * F::L;
+}
+template <typename TS, int M, int j> __device__ __forceinline__ float *top_r(char *lds, int x) {
+    using F = FuseTop<TS, M>;
+    return reinterpret_cast<float *>(lds + F::r_off) +
+           (((j & 1) ? F::r_region(0) : 0) + (x - 1) * (1 << j) * F::ch) * F::L;
+}
+
+template <typename TS, int M, int j>
+__device__ __forceinline__ void fuse_top_up(const FuseArgs &a, const FuseTile &t, char *lds, int own,
+                                            int sb, int tid) {
+    using F = FuseTop<TS, M>;
+    using C = typename Store<TS>::C;
+    constexpr int V = F::V, L = F::L, H = F::H, NW = F::NW, pdirs = (1 << (j - 1)) + 1;
+    const int N = a.N, S = 1 << N, m = a.n + j;
+    const int wave = __builtin_amdgcn_readfirstlane(tid >> 6), lane = tid & 63;
+    const bool last = t.ii == (1 << a.n) - 1;
+    TS *out = reinterpret_cast<TS *>(a.T[j]);
+    for (int i = wave; i < F::cols(j) * pdirs * H; i += NW) {
+        const int h = i % H, e = i / H, X = 1 + e / pdirs, k = e % pdirs;
+        const bool two = k + 1 < pdirs;
+        const Rows<V> w((h * 64 + lane) * V, t.y0, sb, S);
+        const int y = w.y((X << j) - 1);
+        // T_n's odd columns lie first, so its far column is 2^(M-1) - 1 columns back
+        constexpr int far = j == 1 ? (1 - (1 << (M - 1))) * 2 * L : pdirs * L;
+        C ev[V], od[V];
+        fused_up<TS, V, L, true>(top_t<TS, M, j - 1>(lds, 2 * X) + k * L + w.r, far, k, w,
+                                 y + (sb << (j - 1)), ev, od);
+        TS *d = top_t<TS, M, j>(lds, X) + 2 * k * L + w.r;
+        st_row<V>(d, ev);
+        if (two) st_row<V>(d + L, od);
+        if (out && w.r < own) {
+            TS *o = out + ((unsigned)t.q * t_entries(N, m) +
+                           ((unsigned)(X * ((1 << m) + 1) + (t.ii << j) + 2 * k) << N));
+            if (two || last) st_row<V>(o + (unsigned)y, ev);
+            if (two) st_row<V>(o + (unsigned)(y + S), od);
+        }
+    }
+}
+
+template <typename TS, int M, int j>
+__device__ __forceinline__ void fuse_top_down(const FuseArgs &a, const FuseTile &t, char *lds,
+                                              int own, int sb, int tid) {
+    using F = FuseTop<TS, M>;
+    using C = typename Store<TS>::C;
+    constexpr int V = F::V, L = F::L, H = F::H, NW = F::NW, CH = F::ch, cones = 1 << j;
+    const int N = a.N, S = 1 << N, nn = a.n + j;  // output level
+    const int wave = __builtin_amdgcn_readfirstlane(tid >> 6), lane = tid & 63;
+    const float4 *wl = reinterpret_cast<const float4 *>(lds + F::w_off) + cones - 1;
+    float *out = a.R[j];
+    const size_t plane = (size_t)a.nq << (2 * N);
+    for (int i = wave; i < F::cols(j) * cones * H; i += NW) {
+        const int h = i % H, e = i / H, x = 1 + e / cones, k = e % cones;
+        const Rows<V> w((h * 64 + lane) * V, t.y0, sb, S);
+        const int y = w.y((x << j) - 1);
+        const float4 wt = wl[k];
+        float o[CH][V];
+        if (x & 1) {
+            const TS *tb = top_t<TS, M, j>(lds, x) + k * L + w.r;
+            const int yv = y + (sb << j);
+            if constexpr (j + 1 < M) {
+                // a probe past the last column is the light from beyond the grid
+                const int c = (x + 1) >> 1, cc = c <= F::cols(j + 1) ? c : c - 1;
+                const float *rm = top_r<TS, M, j + 1>(lds, cc > 0 ? cc : 1) + (2 * CH * L + 2) * k + w.r;
+                fused_down_odd<TS, V, L>(tb, rm, c <= F::cols(j + 1), k, wt, w, yv, o);
+            } else {
+                // R_N is the light from beyond the grid
+                C tv[2][V];
+#pragma unroll
+                for (int up = 0; up < 2; ++up) ld_row<V>(tb + up * L, tv[up]);
+#pragma unroll
+                for (int c = 0; c < CH; ++c)
+#pragma unroll
+                    for (int v = 0; v < V; ++v) {
+                        o[c][v] = 0.f;
+                        o[c][v] += fmaf(trans(tv[0][v]), wt.y, wt.x * rad(tv[0][v], c));
+                        o[c][v] += fmaf(trans(tv[1][v]), wt.w, wt.z * rad(tv[1][v], c));
+                    }
+            }
+        } else {
+            if constexpr (j + 1 < M) {
+                const int cc = x >> 1;
+                const bool far = cc + 1 <= F::cols(j + 1);
+                C ed[2][V];
+#pragma unroll
+                for (int up = 0; up < 2; ++up)
+                    ld_row<V>(top_t<TS, M, j + 1>(lds, cc) + 2 * (k + up) * L + w.r, ed[up]);
+                const float *rn = top_r<TS, M, j + 1>(lds, cc) + 2 * CH * L * k + w.r;
+                const float *rf = rn + (far ? (2 << j) * CH * L : 0) + 4 * k;
+                fused_down_even<TS, V, L>(ed, rn, rf, far, k, wt, w, y + 2 * (sb << j), o);
+            }
+        }
+        if constexpr (j > 0) {
+            float *dst = top_r<TS, M, j>(lds, x) + k * CH * L + w.r;
+#pragma unroll
+            for (int c2 = 0; c2 < CH; ++c2) st_f<V>(dst + c2 * L, o[c2]);
+        }
+        if ((j == 0 || out) && w.r < own) {
+            float *op = out + (((unsigned)t.q << (2 * N)) +
+                               ((unsigned)((x << nn) | ((t.ii << j) + k)) << N));
+#pragma unroll
+            for (int c2 = 0; c2 < CH; ++c2) st_f<V>(op + c2 * plane + (unsigned)y, o[c2]);
+        }
+    }
+}
+
+template <typename TS, int M>
+__device__ __forceinline__ void fuse_top_block(const FuseArgs &a, unsigned tile, char *lds, int tid) {
+    using F = FuseTop<TS, M>;
+    const int N = a.N, S = 1 << N, n = a.n;
+    const FuseTile t = fuse_tile(a, tile);
+    const int sb = 2 * t.ii - (1 << n);
+    const int own = a.win < S - t.y0 ? a.win : S - t.y0;
+    load_weights<M>(reinterpret_cast<float4 *>(lds + F::w_off), n, t.ii,
+                    a.env ? a.env + (size_t)(a.q0 + t.q) * kConeTable : nullptr, tid);
+    load_tn<TS, F::V, F::L, F::NT, F::cols(0)>(
+        reinterpret_cast<const TS *>(a.T[0]) + (unsigned)t.q * t_entries(N, n),
+        reinterpret_cast<TS *>(lds), N, n, t.ii, 1, 1, t.y0, sb, tid,
+        [](int i) { return F::slot(i + 1); });
+    __syncthreads();
+    fuse_top_up<TS, M, 1>(a, t, lds, own, sb, tid);
+    __syncthreads();
+    if constexpr (M >= 3) {
+        fuse_top_up<TS, M, 2>(a, t, lds, own, sb, tid);
+        __syncthreads();
+    }
+    if constexpr (M >= 4) {
+        fuse_top_up<TS, M, 3>(a, t, lds, own, sb, tid);
+        __syncthreads();
+        fuse_top_down<TS, M, 3>(a, t, lds, own, sb, tid);
+        __syncthreads();
+    }
+    if constexpr (M >= 3) {
+        fuse_top_down<TS, M, 2>(a, t, lds, own, sb, tid);
+        __syncthreads();
+    }
+    fuse_top_down<TS, M, 1>(a, t, lds, own, sb, tid);
+    __syncthreads();
+    fuse_top_down<TS, M, 0>(a, t, lds, own, sb, tid);
+}
+
+// ---- merge down of two levels: (T_n, R_{n+2}) -> R_n, n >= 2 -------------------------
+
+// A block computes R_n at the columns x0 + 1 .. x0 + CC (x0 a multiple of CC) of
+// one cone: these read columns 1 .. CC/2 + 1 (from x0/2) of R_{n+1} and 1 ..
+// CC/4 + 1 (from x0/4) of R_{n+2}; T_{n+1}, and the even directions of
+// T_{n+2}, are rebuilt from T_n's columns x0 + 1 .. x0 + CC + 3.  R_{n+1} lies
+// over the columns of T_n that only the rebuild reads.
+template <typename TS> struct FuseDown {
+    static constexpr int L = 128, V = sizeof(TS) == 16 ? 1 : 2, H = L / (64 * V);
+    static constexpr int NT = 512, NW = NT / 64, ch = Store<TS>::ch;
+    static constexpr int CC = sizeof(TS) == 16 ? 4 : 8;
+    static constexpr int win = L - 2 * (CC + 3);
+    static constexpr int c0 = CC + 3, c1 = CC / 2 + 1, c2 = CC / 4 + 1;  // columns per level
+    static constexpr int t0_rows = 2 * c0, t1_rows = 3 * c1;
+    static constexpr int odd_bytes = (CC / 2) * 2 * L * (int)sizeof(TS);
+    static constexpr int t_bytes = (t0_rows + t1_rows) * L * (int)sizeof(TS);
+    static constexpr int r2_bytes = c2 * 4 * ch * L * 4, r1_bytes = c1 * 2 * ch * L * 4;
+    static constexpr bool overlay = t0_rows * L * (int)sizeof(TS) - odd_bytes >= r1_bytes;
+    static constexpr int r1_off = overlay ? odd_bytes : t_bytes + r2_bytes;
+    static constexpr int w_off =
+        t_bytes + r2_bytes + (overlay ? 0 : r1_bytes) + kFusePad * (int)sizeof(TS);
+    static constexpr int lds = w_off + 16 * 3;
+    // LDS column of T_n's column x0 + i: the odd ones below CC first, then the
+    // rest in order
+    __device__ __forceinline__ static int slot(int i) {
+        return i >= CC ? i - 1 : (i & 1) ? i >> 1 : CC / 2 + (i >> 1) - 1;
+    }
+};
+
+template <typename TS>
+__device__ __forceinline__ void fuse_down_block(const FuseArgs &a, unsigned tile, char *lds, int tid) {
+    using F = FuseDown<TS>;
+    using C = typename Store<TS>::C;
+    constexpr int V = F::V, L = F::L, H = F::H, NW = F::NW, CH = F::ch, CC = F::CC;
+    const int N = a.N, S = 1 << N, n = a.n;
+    const FuseTile t = fuse_tile(a, tile);
+    const int x0 = t.x * CC, cols = S >> n;
+    const int sb = 2 * t.ii - (1 << n);
+    const int own = a.win < S - t.y0 ? a.win : S - t.y0;
+    const size_t plane = (size_t)a.nq << (2 * N);
+    const int wave = __builtin_amdgcn_readfirstlane(tid >> 6), lane = tid & 63;
+    TS *t0 = reinterpret_cast<TS *>(lds), *t1 = t0 + F::t0_rows * L;
+    float *r2 = reinterpret_cast<float *>(lds + F::t_bytes);
+    float *r1 = reinterpret_cast<float *>(lds + F::r1_off);
+    float4 *wl = reinterpret_cast<float4 *>(lds + F::w_off);
+    auto t0_col = [&](int i) { return t0 + F::slot(i) * 2 * L; };
+    auto t1_col = [&](int i) { return t1 + (i - 1) * 3 * L; };
+    auto r2_col = [&](int i) { return r2 + (i - 1) * 4 * CH * L; };
+    auto r1_col = [&](int i) { return r1 + (i - 1) * 2 * CH * L; };
+    load_weights<2>(wl, n, t.ii, a.env ? a.env + (size_t)(a.q0 + t.q) * kConeTable : nullptr, tid);
+    // R_{n+2} into LDS (its loads in flight with T_n's)
+    {
+        constexpr int ROWS = F::c2 * 4 * CH * H, IT = (ROWS + NW - 1) / NW;
+        using Raw = typename RawVec<4 * V>::type;
+        Raw v[IT];
+        const float *R2 = a.R[2] + ((unsigned)t.q << (2 * N));
+#pragma unroll
+        for (int it = 0; it < IT; ++it) {
+            const int i = it * NW + wave;
+            if (i < ROWS) {
+                const int h = i % H, e = i / H, pl = e % CH, k = (e / CH) & 3, c = 1 + e / (4 * CH);
+                const Rows<V> w((h * 64 + lane) * V, t.y0, sb, S);
+                const int X = (x0 >> 2) + c, last = (cols >> 2) - 1;
+                v[it] = *reinterpret_cast<const Raw *>(
+                    R2 + pl * plane +
+                    (((unsigned)(((X < last ? X : last) << (n + 2)) | (4 * t.ii + k)) << N) +
+                     (unsigned)w.y(4 * c - 1)));
+            }
+        }
+        load_tn<TS, V, L, F::NT, F::c0>(
+            reinterpret_cast<const TS *>(a.T[0]) + (unsigned)t.q * t_entries(N, n), t0, N, n, t.ii,
+            x0 + 1, x0 + 1, t.y0, sb, tid, [](int i) { return F::slot(i + 1); });
+#pragma unroll
+        for (int it = 0; it < IT; ++it) {
+            const int i = it * NW + wave;
+            if (i < ROWS)
+                *reinterpret_cast<Raw *>(r2 + (i / H) * L + ((i % H) * 64 + lane) * V) = v[it];
+        }
+    }
+    __syncthreads();
+    // T_{n+1}: directions 0, 1 and direction 2 of every column
+    for (int i = wave; i < F::c1 * 2 * H; i += NW) {
+        const int h = i % H, e = i / H, X = 1 + (e >> 1), k = e & 1;
+        const Rows<V> w((h * 64 + lane) * V, t.y0, sb, S);
+        const int far = (int)(t0_col(2 * X + 1) - t0_col(2 * X));
+        C ev[V], od[V];
+        fused_up<TS, V, L, true>(t0_col(2 * X) + k * L + w.r, far, k, w, w.y(2 * X - 1) + sb, ev, od);
+        TS *d = t1_col(X) + 2 * k * L + w.r;
+        st_row<V>(d, ev);
+        if (k == 0) st_row<V>(d + L, od);
+    }
+    __syncthreads();
+    // R_{n+1}
+    for (int i = wave; i < F::c1 * 2 * H; i += NW) {
+        const int h = i % H, e = i / H, x = 1 + (e >> 1), k = e & 1;
+        if ((x0 >> 1) + x >= (cols >> 1)) continue;  // beyond the grid: read by no one
+        const Rows<V> w((h * 64 + lane) * V, t.y0, sb, S);
+        const int y = w.y(2 * x - 1);
+        const float4 wt = wl[1 + k];
+        const int c = (x + 1) >> 1;
+        float o[CH][V];
+        if (x & 1) {
+            fused_down_odd<TS, V, L>(t1_col(x) + k * L + w.r, r2_col(c) + (2 * CH * L + 2) * k + w.r,
+                                     (x0 >> 2) + c < (cols >> 2), k, wt, w, y + 2 * sb, o);
+        } else {
+            const int cc = x >> 1;
+            C ed[2][V], none[V];
+#pragma unroll
+            for (int up = 0; up < 2; ++up) {
+                fused_up<TS, V, L, false>(t1_col(2 * cc) + (k + up) * L + w.r, 3 * L, k + up, w,
+                                          y + 2 * sb, ed[up], none);
+#pragma unroll
+                for (int j = 0; j < V; ++j) ed[up][j] = stored(ed[up][j], static_cast<const TS *>(nullptr));
+            }
+            const float *rn = r2_col(cc) + 2 * CH * L * k + w.r;
+            fused_down_even<TS, V, L>(ed, rn, rn + 4 * CH * L + 4 * k, (x0 >> 2) + cc + 1 < (cols >> 2),
+                                      k, wt, w, y + 4 * sb, o);
+        }
+        float *dst = r1_col(x) + k * CH * L + w.r;
+#pragma unroll
+        for (int c2 = 0; c2 < CH; ++c2) st_f<V>(dst + c2 * L, o[c2]);
+        if (a.R[1] && x <= CC / 2 && w.r < own) {
+            float *out = a.R[1] + (((unsigned)t.q << (2 * N)) +
+                                   ((unsigned)((((x0 >> 1) + x) << (n + 1)) | (2 * t.ii + k)) << N));
+#pragma unroll
+            for (int c2 = 0; c2 < CH; ++c2) st_f<V>(out + c2 * plane + (unsigned)y, o[c2]);
+        }
+    }
+    __syncthreads();
+    // R_n
+    for (int i = wave; i < CC * H; i += NW) {
+        const int h = i % H, x = 1 + i / H;
+        if (x0 + x >= cols) continue;
+        const Rows<V> w((h * 64 + lane) * V, t.y0, sb, S);
+        const int y = w.y(x - 1);
+        const float4 wt = wl[0];
+        const int c = (x + 1) >> 1;
+        float o[CH][V];
+        if (x & 1) {
+            fused_down_odd<TS, V, L>(t0_col(x) + w.r, r1_col(c) + w.r, (x0 >> 1) + c < (cols >> 1), 0,
+                                     wt, w, y + sb, o);
+        } else {
+            const int cc = x >> 1;
+            C ed[2][V];
+#pragma unroll
+            for (int up = 0; up < 2; ++up) ld_row<V>(t1_col(cc) + 2 * up * L + w.r, ed[up]);
+            const float *rn = r1_col(cc) + w.r;
+            fused_down_even<TS, V, L>(ed, rn, rn + 2 * CH * L, (x0 >> 1) + cc + 1 < (cols >> 1), 0, wt,
+                                      w, y + 2 * sb, o);
+        }
+        if (w.r < own) {
+            float *out = a.R[0] + (((unsigned)t.q << (2 * N)) +
+                                   ((unsigned)(((x0 + x) << n) | t.ii) << N));
+#pragma unroll
+            for (int c2 = 0; c2 < CH; ++c2) st_f<V>(out + c2 * plane + (unsigned)y, o[c2]);
+        }
+    }
+}

@@ -142,12 +142,30 @@ struct BlurArgs {
     float thr;
 };
 
+// Several levels of the merges in one kernel (see hrc_fused.h), all pointers at
+// the group's first quadrant:
+//   up    T[0] = T_n -> T_{n+1} .. T_{n+levels}: T[j] = T_{n+j} where it is
+//         stored (the last always is), NULL where it stays on chip
+//   top   T[0] = T_n, levels = N - n: T[j] and R[j] as above (R[0] = R_n always)
+//   down  T[0] = T_n, R[2] = R_{n+2} read; R[0] = R_n, R[1] = R_{n+1} or NULL
+struct FuseArgs {
+    void *T[5];
+    float *R[4];
+    const float *env;  // environment table (nullable)
+    int N, n, levels, nq, q0;
+    int win, nwin;     // rows of a window that are stored, windows over the grid
+    int chunks;        // column chunks
+    int half, rgb;     // interval storage
+};
+
 enum PhaseKind {
     PH_SEED = 0, PH_UP, PH_DOWN, PH_TAIL, PH_GATHER_ADJ,
     PH_DOWN_ADJ, PH_DT, PH_SEED_ADJ, PH_BLUR, PH_BLUR_ADJ,
     // the RGB solve (three radiance channels over one medium) and its reverse
     PH_SEED_RGB, PH_UP_RGB, PH_DOWN_RGB, PH_TAIL_RGB,
-    PH_DOWN_ADJ_RGB, PH_DT_RGB, PH_SEED_ADJ_RGB, PH_KIND_COUNT
+    PH_DOWN_ADJ_RGB, PH_DT_RGB, PH_SEED_ADJ_RGB,
+    // several levels of the merges in one kernel
+    PH_FUSE_UP, PH_FUSE_TOP, PH_FUSE_DOWN, PH_KIND_COUNT
 };
 
 // One pass.  U = elements per thread of the elementwise phases (a tile covers
@@ -166,6 +184,7 @@ struct Phase {
         DTArgs dt;
         SeedAdjArgs sa;
         BlurArgs bl;
+        FuseArgs fu;
         A() : dt{} {}
     } a;
 };
@@ -187,8 +206,10 @@ constexpr float kBlurThreshold = 0.5f;
 // keep_all_r: the reverse's layout, every level kept (forward down to R_1).
 // recompute = false (with keep_all_r and a gradient): only the reverse, on
 // the levels a kept forward left in the workspace.
+// fused = false: every merge level a pass of its own (the persistent kernel
+// runs those; the results are bitwise the same).
 int build_solve_phases(const Ws &w, const SolveBuffers &b, bool keep_all_r, const int *U,
-                       Phase *out, int max_out, bool recompute = true);
+                       Phase *out, int max_out, bool recompute = true, bool fused = true);
 // The passes of one RGB forward (all four quadrants at once): eps is [3][S][S],
 // F is [3][S][S]; with blur, each plane is blurred by the one-channel pass.
 int build_rgb_forward_phases(const Ws &w, const SolveBuffers &b, Phase *out, int max_out);
@@ -197,6 +218,8 @@ int build_rgb_forward_phases(const Ws &w, const SolveBuffers &b, Phase *out, int
 int build_rgb_backward_phases(const Ws &w, const SolveBuffers &b, Phase *out, int max_out,
                               bool recompute);
 
+// Sets the window of a fused phase (its levels, storage and N set) and its chunks.
+void size_fused(Phase &p);
 unsigned phase_tiles(const Phase &p);
 hipError_t upload_cone_table(const float *host_table);
 // Launches one pass.  With events, they are recorded at the kernel's own start

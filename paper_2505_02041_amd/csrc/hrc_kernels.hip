@@ -26,6 +26,8 @@
 // no atomics.
 #include <hip/hip_ext.h>
 
+#include <type_traits>
+
 #include "hrc_internal.h"
 
 namespace hrc {
@@ -1150,11 +1152,12 @@ __device__ void body_merge_down_adj(const DownAdjArgs &a, unsigned tile, int U, 
                 g = make_float2(in0 ? ga : 0.f, in1 ? gb : 0.f);
                 t = make_float2(in0 ? ta : 0.f, in1 ? tb : 0.f);
             }
-            // even column 2c-2 (far end of Eq. 17) at row y' - (2 e2 - 2^(n+1))
+            // even column 2c-2 (far end of Eq. 17) at row y' - (2 e2 - 2^(n+1));
+            // column 0 (c = 1) has no adjoint, and the forward no T there
             const int e2 = 2 * ii + 2 * up;
             const int x2 = 2 * c - 2;
             const int y2 = yp - (2 * e2 - (1 << m));
-            const bool in2 = (unsigned)y2 < (unsigned)S;
+            const bool in2 = c > 1 && (unsigned)y2 < (unsigned)S;
             const int y2c = in2 ? y2 : 0;
             const float2 g2v = *reinterpret_cast<const float2 *>(
                 a.dR + (qS + ((unsigned)((x2 << n) | ii) << N) + (unsigned)y2c));
@@ -1258,7 +1261,9 @@ __device__ __forceinline__ void dT_output(const DTArgs &a, int q, int x, int k, 
             const int ko = v == 0 ? 2 * k : (v == 1 ? 2 * k + 1 : 2 * k - 1);
             const int kp = v == 0 ? k : (v == 1 ? k + 1 : k - 1);
             const int yo = near_role ? y + 2 * k - H : y - (2 * kp - H);
-            act[v] = ko >= 0 && ko <= 2 * H;
+            // none in the far role at x = 1: dT_{n+1} is 0 at column 0, where
+            // the forward keeps no T
+            act[v] = ko >= 0 && ko <= 2 * H && x != 1;
             in[v] = (unsigned)yo < (unsigned)S;
             const int yc = in[v] ? yo : 0;
             cr[v] = raw_zero<TS>();
@@ -2227,9 +2232,10 @@ __device__ void body_merge_down_adj_rgb(const DownAdjArgs &a, unsigned tile, int
                 t = make_float2(in0 ? ta : 0.f, in1 ? tb : 0.f);
             }
             // even column 2c-2 (far end of Eq. 17) at row y' - (2 e2 - 2^(n+1))
+            // (none from column 0, c = 1: as body_merge_down_adj)
             const int e2 = 2 * ii + 2 * up, x2 = 2 * c - 2;
             const int y2 = yp - (2 * e2 - (1 << m));
-            const bool in2 = (unsigned)y2 < (unsigned)S;
+            const bool in2 = c > 1 && (unsigned)y2 < (unsigned)S;
             const int y2c = in2 ? y2 : 0;
             const TS *t2row = reinterpret_cast<const TS *>(a.Tn1) + q * a.en1 +
                               ((size_t)(c - 1) * ((1 << m) + 1) + e2) * S;
@@ -2347,7 +2353,7 @@ __device__ void body_dT_rgb(const DTArgs &a, unsigned tile, int U, int tid) {
             for (int v = 0; v < 3; ++v) {
                 const int ko = v == 0 ? 2 * k : (v == 1 ? 2 * k + 1 : 2 * k - 1);
                 const int kp = v == 0 ? k : (v == 1 ? k + 1 : k - 1);
-                if (ko < 0 || ko > 2 * H) continue;
+                if (ko < 0 || ko > 2 * H || x == 1) continue;  // x = 1: as dT_output
                 cw[v] = v == 0 ? 1.f : 0.5f;
                 if (near_role) {
                     far_pair_rgb(part + (size_t)kp * S, y + 2 * k - H, S, cf[v][0], cf[v][1]);
@@ -2593,6 +2599,8 @@ __device__ __forceinline__ void body_seed_adj_rgb(const SeedAdjArgs &a, unsigned
     __syncthreads();
 }
 
+#include "hrc_fused.h"
+
 // The persistent kernel's one LDS buffer: the largest body it runs (the traced
 // levels and the tail run there on 16x16 tiles).
 constexpr int kMaxLds2 = kSeedAdjLds > SeedTile<16>::lds ? kSeedAdjLds : SeedTile<16>::lds;
@@ -2709,6 +2717,66 @@ __global__ __launch_bounds__(256) void hrc_seed_adj_rgb(Phase p) {
 __global__ __launch_bounds__(256) void hrc_gather_adj(Phase p) {
     __shared__ __align__(16) char lds[kGatherAdjLds];
     body_gather_adj(p.a.ga, blockIdx.x, lds, ltid());
+}
+
+template <typename TS, int G>
+__global__ __launch_bounds__((FuseUp<TS, G>::NT)) void hrc_fuse_up(Phase p) {
+    __shared__ __align__(16) char lds[FuseUp<TS, G>::lds];
+    fuse_up_block<TS, G>(p.a.fu, xcd_tile_blk(blockIdx.x, gridDim.x, p.xblk), lds, (int)threadIdx.x);
+}
+template <typename TS, int M>
+__global__ __launch_bounds__((FuseTop<TS, M>::NT)) void hrc_fuse_top(Phase p) {
+    __shared__ __align__(16) char lds[FuseTop<TS, M>::lds];
+    fuse_top_block<TS, M>(p.a.fu, xcd_tile_blk(blockIdx.x, gridDim.x, p.xblk), lds,
+                             (int)threadIdx.x);
+}
+template <typename TS>
+__global__ __launch_bounds__(FuseDown<TS>::NT) void hrc_fuse_down(Phase p) {
+    __shared__ __align__(16) char lds[FuseDown<TS>::lds];
+    fuse_down_block<TS>(p.a.fu, xcd_tile_blk(blockIdx.x, gridDim.x, p.xblk), lds, (int)threadIdx.x);
+}
+
+// Kernel, block size and window of a fused phase.
+struct FusedKernel {
+    void (*k)(Phase);
+    int threads, win;  // the most window rows a block stores
+};
+template <typename TS> FusedKernel fused_kernel_t(const Phase &p) {
+    const FuseArgs &a = p.a.fu;
+    auto up = [](auto g) {
+        using F = FuseUp<TS, decltype(g)::value>;
+        return FusedKernel{hrc_fuse_up<TS, decltype(g)::value>, F::NT, F::win};
+    };
+    auto top = [](auto m) {
+        using F = FuseTop<TS, decltype(m)::value>;
+        return FusedKernel{hrc_fuse_top<TS, decltype(m)::value>, F::NT, F::win};
+    };
+    using std::integral_constant;
+    integral_constant<int, 2> i2;
+    integral_constant<int, 3> i3;
+    integral_constant<int, 4> i4;
+    if (p.kind == PH_FUSE_UP) {
+        if (a.levels == 2) return up(i2);
+        if (a.levels == 3) return up(i3);
+        if constexpr (sizeof(TS) <= 8 && Store<TS>::ch == 1)
+            if (a.levels == 4) return up(i4);
+    } else if (p.kind == PH_FUSE_TOP) {
+        if (a.levels == 2) return top(i2);
+        if (a.levels == 3) return top(i3);
+        if constexpr (Store<TS>::ch == 1)
+            if (a.levels == 4) return top(i4);
+    } else if (p.kind == PH_FUSE_DOWN) {
+        return FusedKernel{hrc_fuse_down<TS>, FuseDown<TS>::NT, FuseDown<TS>::win};
+    }
+    return FusedKernel{nullptr, 0, 0};
+}
+static FusedKernel fused_kernel(const Phase &p) {
+    const FuseArgs &a = p.a.fu;
+    if (a.rgb) return a.half ? fused_kernel_t<half4_t>(p) : fused_kernel_t<float4>(p);
+    return a.half ? fused_kernel_t<half2_t>(p) : fused_kernel_t<float2>(p);
+}
+static bool is_fused(const Phase &p) {
+    return p.kind == PH_FUSE_UP || p.kind == PH_FUSE_TOP || p.kind == PH_FUSE_DOWN;
 }
 
 // ---------------------------------------------------------------------------
@@ -2934,7 +3002,25 @@ __global__ __launch_bounds__(256) void hrc_validate(const float *a, const float 
 // Host-side launchers and phase builders
 // ---------------------------------------------------------------------------
 
+void size_fused(Phase &p) {
+    FuseArgs &a = p.a.fu;
+    const FusedKernel f = fused_kernel(p);
+    const int S = 1 << a.N;
+    a.nwin = (S + f.win - 1) / f.win;
+    a.win = (S / 2 + a.nwin - 1) / a.nwin * 2;  // even, the windows of equal size
+    if (p.kind == PH_FUSE_UP)
+        a.chunks = S >> (a.n + a.levels);
+    else if (p.kind == PH_FUSE_DOWN)
+        a.chunks = (S >> a.n) / (a.rgb && !a.half ? FuseDown<float4>::CC : FuseDown<float2>::CC);
+    else
+        a.chunks = 1;
+}
+
 unsigned phase_tiles(const Phase &p) {
+    if (is_fused(p)) {
+        const FuseArgs &a = p.a.fu;
+        return (unsigned)a.nq * (unsigned)a.chunks * ((unsigned)a.nwin << a.n);
+    }
     auto cdiv = [](size_t a, size_t b) { return (unsigned)((a + b - 1) / b); };
     const int N = [&] {
         switch (p.kind) {
@@ -3002,6 +3088,7 @@ hipError_t launch_phase(const Phase &p, hipStream_t s, hipEvent_t start, hipEven
     unsigned tiles = phase_tiles(p);
     if (tiles == 0) return hipSuccess;
     void (*k)(Phase) = nullptr;
+    unsigned threads = 256;
     switch (p.kind) {
         case PH_SEED: k = p.a.seed.half ? hrc_seed_f16 : hrc_seed; break;
         case PH_UP: k = p.a.up.half ? hrc_merge_up_f16 : hrc_merge_up; break;
@@ -3020,12 +3107,21 @@ hipError_t launch_phase(const Phase &p, hipStream_t s, hipEvent_t start, hipEven
         case PH_DOWN_ADJ_RGB: k = p.a.da.half ? hrc_merge_down_adj_rgb_f16 : hrc_merge_down_adj_rgb; break;
         case PH_DT_RGB: k = p.a.dt.half ? hrc_interval_adj_rgb_f16 : hrc_interval_adj_rgb; break;
         case PH_SEED_ADJ_RGB: k = hrc_seed_adj_rgb; break;
+        case PH_FUSE_UP:
+        case PH_FUSE_TOP:
+        case PH_FUSE_DOWN: {
+            const FusedKernel f = fused_kernel(p);
+            if (!f.k) return hipErrorInvalidValue;
+            k = f.k;
+            threads = (unsigned)f.threads;
+            break;
+        }
         default: return hipErrorInvalidValue;
     }
     if (start || stop)
-        hipExtLaunchKernelGGL(k, dim3(tiles), dim3(256), 0, s, start, stop, 0, p);
+        hipExtLaunchKernelGGL(k, dim3(tiles), dim3(threads), 0, s, start, stop, 0, p);
     else
-        hipLaunchKernelGGL(k, dim3(tiles), dim3(256), 0, s, p);
+        hipLaunchKernelGGL(k, dim3(tiles), dim3(threads), 0, s, p);
     return hipGetLastError();
 }
 
