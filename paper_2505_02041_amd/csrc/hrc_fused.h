@@ -25,14 +25,16 @@
 // Column 0 of a level is read by nothing but column 0 of the levels below,
 // and the gather never reads that: the top and the down kernels leave it out.
 //
-// Measured at 1024^2 (FP32, four quadrants, per forward): T_2 -> T_6 26.9 us
-// (four single levels 40), T_6 -> R_6 31 us (three levels up and four down: 76),
-// R_6 -> R_4 -> R_2 31 us each (24 per two single levels down, but they also
-// save storing T_3 and T_5); forward 217.7 -> 143.3 us, 64^2 37 -> 24 us (3
-// launches for 11), 4096^2 4.37 -> 2.99 ms.  They move 40-60% of the bytes of the
-// single levels and are bound by instruction issue and LDS latency, not HBM:
-// the LDS of a block (58 and 78 KB) leaves two blocks on a CU, so 1024 threads a
-// block (512: 31 and 36 us) keep the 32 waves the CU can hold.
+// Measured at 1024^2 (FP32, four quadrants, per forward): T_2 -> T_4, T_6 23.2 us
+// (four single levels 40), 107 MB at 4.6 TB/s; T_6 -> R_6 28.5 us (three levels up
+// and four down: 76), bound by vector and scalar issue (35 and 40 thousand
+// instructions a CU in 58 thousand cycles); R_6 -> R_4 -> R_2 24 us each (two
+// single levels 24, but those need T_3 and T_5 stored), 67 MB, half HBM and half
+// issue.  Forward 217.7 -> 133 us, 64^2 37 -> 24 us (3 launches for 11).  Block
+// sizes: the LDS of a top or four-level block (78 and 58 KB) leaves two on a CU,
+// so FP32 blocks of 1024 threads fill its 32 waves (512: 32 and 25.6 us); the
+// 16-bit ones fit three to five (1024: 30.5 and 23.8 us, 512: 28.2 and 20.4), and
+// a merge down four (512 threads: 24.0 and 24.8 us, 256: 24.0 and 22.6).
 //
 // The arithmetic of every element, and its order, is that of the
 // level-by-level bodies, and 16-bit intervals are rounded at the same points
@@ -63,6 +65,8 @@ __device__ __forceinline__ float4 half_sum(float4 a, float4 b) {
     return make_float4(0.5f * (a.x + b.x), 0.5f * (a.y + b.y), 0.5f * (a.z + b.z),
                        0.5f * (a.w + b.w));
 }
+
+constexpr int kWindow = 128;  // window rows of an LDS row
 
 // V consecutive intervals of a row as one vector access.
 template <int V> __device__ __forceinline__ void ld_row(const float2 *p, float2 (&o)[V]) {
@@ -147,26 +151,31 @@ __device__ __forceinline__ float4 stored(float4 v, const half4_t *) {
 
 // ---- one block's window -------------------------------------------------------
 
-// The block's quadrant (of the group), cone of level n and first window row.
+// The block's quadrant (of the group), cone of level n, chunk of columns and
+// first window row.
 struct FuseTile {
-    int q, ii, x, y0;  // x: chunk of columns
+    int q, ii, x, y0;
 };
 
 // Tiles in the order cone (its low three bits), window, cone, chunk, quadrant:
 // neighbours in cone share a direction of T_n and neighbours in window their
-// halo rows, so they run side by side on one XCD and meet in its L2.
-__device__ __forceinline__ FuseTile fuse_tile(const FuseArgs &a, unsigned t) {
+// halo rows, so they run side by side on one XCD (each takes a contiguous
+// eighth) and meet in its L2.  Every wave decodes its block's tile in the
+// scalar unit, which the kernels keep nearly as busy as the vector units:
+// shifts, and a multiplication in place of the division by the windows.
+__device__ __forceinline__ FuseTile fuse_tile(const FuseArgs &a) {
+    unsigned t = blockIdx.x;
+    if (a.eighth) t = (t & 7u) * (unsigned)a.eighth + (t >> 3);
     const int lb = a.n < 3 ? a.n : 3;
     FuseTile f;
     f.ii = (int)(t & ((1u << lb) - 1));
     t >>= lb;
-    const unsigned w = t % (unsigned)a.nwin;
-    t /= (unsigned)a.nwin;
-    f.y0 = (int)w * a.win;
-    f.ii |= (int)(t & ((1u << (a.n - lb)) - 1)) << lb;
-    t >>= a.n - lb;
-    f.x = (int)(t % (unsigned)a.chunks);
-    f.q = (int)(t / (unsigned)a.chunks);
+    const unsigned d = a.inv_nwin ? (unsigned)(((unsigned long long)t * a.inv_nwin) >> 32) : t;
+    f.y0 = (int)(t - d * (unsigned)a.nwin) * a.win;
+    f.ii |= (int)(d & ((1u << (a.n - lb)) - 1)) << lb;
+    t = d >> (a.n - lb);
+    f.x = (int)(t & ((1u << a.lchunks) - 1));
+    f.q = (int)(t >> a.lchunks);
     return f;
 }
 
@@ -179,6 +188,12 @@ template <int V> struct Rows {
     __device__ __forceinline__ int y(int p) const { return (base + p * sb) & mask; }
     __device__ __forceinline__ bool in(int yt) const { return (unsigned)yt <= (unsigned)mask; }
 };
+// Whether the rows of a whole window at every column position 0 .. p lie in the
+// grid, unwrapped: then no lookup of the block leaves it, and none needs a select.
+__device__ __forceinline__ bool window_inside(int y0, int p, int sb, int S) {
+    const int d = p * sb;
+    return y0 + (d < 0 ? d : 0) >= 0 && y0 + (d > 0 ? d : 0) + kWindow <= S;
+}
 
 // Directions 2k and 2k + 1 (relative to the block's lower edge) of one column
 // of level m: Eq. 18, and the mean of Eq. 19-20.  nb: the lane's interval of
@@ -187,7 +202,7 @@ template <int V> struct Rows {
 // plus the rows a column of level m - 1 climbs along the lower edge.  The far
 // lookups run 2k rows up for direction k and 2k + 2 for k + 1, so apart from
 // one base each every LDS offset is an immediate.
-template <typename TS, int V, int L, bool ODD>
+template <typename TS, int V, int L, bool ODD, bool IN>
 __device__ __forceinline__ void fused_up(const TS *nb, int far, int k, const Rows<V> &w, int yv,
                                          typename Store<TS>::C (&even)[V],
                                          typename Store<TS>::C (&odd)[V]) {
@@ -201,21 +216,63 @@ __device__ __forceinline__ void fused_up(const TS *nb, int far, int k, const Row
         ld_row<V>(fb + 2, f02);  // direction k, 2k + 2 rows up
         ld_row<V>(fb + L, f10);  // direction k + 1, 2k rows up
     }
-    const bool in0 = w.in(yv + 2 * k), in1 = w.in(yv + 2 * k + 2);
+    const bool in0 = IN || w.in(yv + 2 * k), in1 = IN || w.in(yv + 2 * k + 2);
+    if constexpr (!IN) {
+        // every read issued before the selects (else each far read becomes a
+        // branch that waits for it)
+#pragma unroll
+        for (int i = 0; i < V; ++i) {
+            pin(f00[i]);
+            if constexpr (ODD) {
+                pin(f02[i]);
+                pin(f10[i]);
+            }
+        }
+        // most waves have every lookup in the grid: one branch spares them the
+        // selects
+        if (!__all(in0 && in1)) {
+#pragma unroll
+            for (int i = 0; i < V; ++i) {
+                f00[i] = in0 ? f00[i] : empty_interval<C>();
+                if constexpr (ODD) {
+                    f02[i] = in1 ? f02[i] : empty_interval<C>();
+                    f10[i] = in0 ? f10[i] : empty_interval<C>();
+                }
+            }
+        }
+    }
 #pragma unroll
     for (int i = 0; i < V; ++i) {
-        even[i] = merge(n0[i], in0 ? f00[i] : empty_interval<C>());
-        if constexpr (ODD)
-            odd[i] = half_sum(merge(n1[i], in1 ? f02[i] : empty_interval<C>()),
-                              merge(n0[i], in0 ? f10[i] : empty_interval<C>()));
+        even[i] = merge(n0[i], f00[i]);
+        if constexpr (ODD) odd[i] = half_sum(merge(n1[i], f02[i]), merge(n0[i], f10[i]));
     }
+}
+
+// The light from beyond the grid (wt.y, wt.w) for the looked-up fluences of the
+// two cones whose probe (far) or row (in0, in1) lies outside.
+template <int CH, int V, bool IN>
+__device__ __forceinline__ void select_light(float (&f)[2][CH][V], bool far, bool in0, bool in1,
+                                             float4 wt) {
+    if (IN && far) return;
+#pragma unroll
+    for (int i = 0; i < 2 * CH * V; ++i) pin(f[i / (CH * V)][i / V % CH][i % V]);
+    in0 = far && (IN || in0);
+    in1 = far && (IN || in1);
+    if (__all(in0 && in1)) return;
+#pragma unroll
+    for (int c = 0; c < CH; ++c)
+#pragma unroll
+        for (int j = 0; j < V; ++j) {
+            f[0][c][j] = in0 ? f[0][c][j] : wt.y;
+            f[1][c][j] = in1 ? f[1][c][j] : wt.w;
+        }
 }
 
 // Eq. 14 (odd column): R_{m-1} of cone k (relative).  t: the lane's interval of
 // direction k of T_{m-1} at this column; rm: the lane's row of cone 2k of R_m at
 // the next probe, 2k rows up (NULL where that probe lies beyond the grid); wt:
 // cone weights and light from beyond the grid of the cones 2k, 2k + 1 (A, E, A, E).
-template <typename TS, int V, int L>
+template <typename TS, int V, int L, bool IN>
 __device__ __forceinline__ void fused_down_odd(const TS *t, const float *rm, bool far, int k,
                                                float4 wt, const Rows<V> &w, int yv,
                                                float (&o)[Store<TS>::ch][V]) {
@@ -229,19 +286,17 @@ __device__ __forceinline__ void fused_down_odd(const TS *t, const float *rm, boo
 #pragma unroll
         for (int c = 0; c < CH; ++c) ld_f<V>(rm + (up * CH + c) * L + 2 * up, f[up][c]);
     }
-#pragma unroll
-    for (int c = 0; c < CH; ++c)
-#pragma unroll
-        for (int j = 0; j < V; ++j) o[c][j] = 0.f;
+    select_light<CH, V, IN>(f, far, w.in(yv + 2 * k), w.in(yv + 2 * k + 2), wt);
 #pragma unroll
     for (int up = 0; up < 2; ++up) {
-        const float A = up ? wt.z : wt.x, E = up ? wt.w : wt.y;
-        const bool in = far && w.in(yv + 2 * (k + up));
+        const float A = up ? wt.z : wt.x;
 #pragma unroll
         for (int c = 0; c < CH; ++c)
 #pragma unroll
-            for (int j = 0; j < V; ++j)
-                o[c][j] += fmaf(trans(tv[up][j]), in ? f[up][c][j] : E, A * rad(tv[up][j], c));
+            for (int j = 0; j < V; ++j) {
+                const float v = fmaf(trans(tv[up][j]), f[up][c][j], A * rad(tv[up][j], c));
+                o[c][j] = up ? o[c][j] + v : v;
+            }
     }
 }
 
@@ -249,7 +304,7 @@ __device__ __forceinline__ void fused_down_odd(const TS *t, const float *rm, boo
 // doubled edges T_m(c, 2k), T_m(c, 2k + 2) (e: already in registers) to the
 // probe c + 1.  rn: the lane's row of cone 2k at probe c; rf: of cone 2k at probe
 // c + 1, 4k rows up (far: that probe lies in the grid).
-template <typename TS, int V, int L>
+template <typename TS, int V, int L, bool IN>
 __device__ __forceinline__ void fused_down_even(const typename Store<TS>::C (&e)[2][V],
                                                 const float *rn, const float *rf, bool far, int k,
                                                 float4 wt, const Rows<V> &w, int yv,
@@ -263,75 +318,75 @@ __device__ __forceinline__ void fused_down_even(const typename Store<TS>::C (&e)
             ld_f<V>(rn + (up * CH + c) * L, f0[up][c]);
             ld_f<V>(rf + (up * CH + c) * L + 4 * up, f1[up][c]);
         }
-#pragma unroll
-    for (int c = 0; c < CH; ++c)
-#pragma unroll
-        for (int j = 0; j < V; ++j) o[c][j] = 0.f;
+    select_light<CH, V, IN>(f1, far, w.in(yv + 4 * k), w.in(yv + 4 * k + 4), wt);
 #pragma unroll
     for (int up = 0; up < 2; ++up) {
-        const float A = up ? wt.z : wt.x, E = up ? wt.w : wt.y;
-        const bool in = far && w.in(yv + 4 * (k + up));
+        const float A = up ? wt.z : wt.x;
 #pragma unroll
         for (int c = 0; c < CH; ++c)
 #pragma unroll
-            for (int j = 0; j < V; ++j)
-                o[c][j] += 0.5f * (f0[up][c][j] + fmaf(trans(e[up][j]), in ? f1[up][c][j] : E,
-                                                       A * rad(e[up][j], c)));
+            for (int j = 0; j < V; ++j) {
+                const float v = 0.5f * (f0[up][c][j] +
+                                        fmaf(trans(e[up][j]), f1[up][c][j], A * rad(e[up][j], c)));
+                o[c][j] = up ? o[c][j] + v : v;
+            }
     }
 }
 
 // Cone weights and light from beyond the grid of every cone pair of the levels
-// n .. n + M - 1 of the block's cone: entry 2^j - 1 + k for cone k of level n + j.
+// n .. n + M - 1 of the block's cone: entry 2^j - 1 + k for cone k of level n + j,
+// thread t's entry t (the threads past the last repeat it).
 template <int M>
-__device__ __forceinline__ void load_weights(float4 *wl, int n, int ii, const float *envq, int tid) {
-    if (tid < (1 << M) - 1) {
-        const int j = 31 - __clz(tid + 1), k = tid + 1 - (1 << j);
-        const int cone = (2 << (n + j)) - 1 + (((ii << j) + k) << 1);
-        wl[tid] = make_float4(c_cone[cone], envq ? envq[cone] : 0.f, c_cone[cone + 1],
-                              envq ? envq[cone + 1] : 0.f);
+__device__ __forceinline__ float4 load_weight(int n, int ii, const float *envq, int tid) {
+    const int t = tid < (1 << M) - 1 ? tid : (1 << M) - 2;
+    const int j = 31 - __clz(t + 1), k = t + 1 - (1 << j);
+    const int cone = (2 << (n + j)) - 1 + (((ii << j) + k) << 1);
+    float4 w = make_float4(c_cone[cone], 0.f, c_cone[cone + 1], 0.f);
+    if (envq) {
+        w.y = envq[cone];
+        w.w = envq[cone + 1];
     }
+    return w;
 }
 // Lookups of rows past the valid ones run up to this many rows past an LDS row
 // (and past the last one: the padding of every buffer).
 constexpr int kFusePad = 64;
 
-// Entries per quadrant of level n (below 2^25 for S <= 4096).
-__device__ __forceinline__ unsigned t_entries(int N, int n) {
-    return (((1u << N) >> n) * ((1u << n) + 1)) << N;
-}
-
-// Rows x of `cols` columns x 2 directions of T_n (columns first_col ..) into
-// LDS: row slot(x) * 2 + d holds direction ii + d.  Every load of a thread is
-// issued before the first is written.  Columns at or past the grid's last are
-// left out.
-template <typename TS, int V, int L, int NT, int COLS, typename Slot>
-__device__ __forceinline__ void load_tn(const TS *T, TS *lds, int N, int n, int ii, int first_col,
-                                        int anchor, int y0, int sb, int tid, Slot slot) {
+// Two directions of COLS columns of T_n into LDS, in two halves so that other
+// loads can be issued between: load() takes the columns first_col .. into
+// registers, store() puts direction ii + d of column i into LDS row
+// 2 slot(i) + d.  No branches (a wave past the last row repeats it), so that
+// every load is in flight before the first wait.  Columns past the grid's last
+// repeat it (and feed no stored value).
+template <typename TS, int V, int L, int NT, int COLS> struct TnLoad {
     using Raw = typename RawVec<sizeof(TS) * V>::type;
-    constexpr int H = L / (64 * V), ROWS = COLS * 2 * H, NW = NT / 64, IT = (ROWS + NW - 1) / NW;
-    const int S = 1 << N, wave = __builtin_amdgcn_readfirstlane(tid >> 6), lane = tid & 63;
-    const int dirs = (1 << n) + 1, C = S >> n;
+    static constexpr int H = L / (64 * V), ROWS = COLS * 2 * H, NW = NT / 64, IT = (ROWS + NW - 1) / NW;
     Raw v[IT];
-#pragma unroll
-    for (int it = 0; it < IT; ++it) {
+    __device__ __forceinline__ static int row(int it, int wave) {
         const int i = it * NW + wave;
-        if (i < ROWS) {
-            const int h = i % H, rd = i / H, x = first_col + (rd >> 1), d = rd & 1;
+        return (it + 1) * NW <= ROWS ? i : i < ROWS ? i : ROWS - 1;
+    }
+    __device__ __forceinline__ void load(const TS *T, int N, int n, int ii, int first_col, int y0,
+                                         int sb, int wave, int lane) {
+        const int S = 1 << N, dirs = (1 << n) + 1, C = S >> n;
+#pragma unroll
+        for (int it = 0; it < IT; ++it) {
+            const int i = row(it, wave), h = i % H, rd = i / H, x = first_col + (rd >> 1), d = rd & 1;
             const Rows<V> w((h * 64 + lane) * V, y0, sb, S);
             const int xc = x < C ? x : C - 1;
             v[it] = *reinterpret_cast<const Raw *>(
-                T + (((unsigned)(xc * dirs + ii + d) << N) + (unsigned)w.y(x - anchor)));
+                T + (((unsigned)(xc * dirs + ii + d) << N) + (unsigned)w.y(rd >> 1)));
         }
     }
+    template <typename Slot>
+    __device__ __forceinline__ void store(TS *lds, int wave, int lane, Slot slot) const {
 #pragma unroll
-    for (int it = 0; it < IT; ++it) {
-        const int i = it * NW + wave;
-        if (i < ROWS) {
-            const int h = i % H, rd = i / H, d = rd & 1;
+        for (int it = 0; it < IT; ++it) {
+            const int i = row(it, wave), h = i % H, rd = i / H, d = rd & 1;
             *reinterpret_cast<Raw *>(lds + (slot(rd >> 1) * 2 + d) * L + (h * 64 + lane) * V) = v[it];
         }
     }
-}
+};
 
 // ---- merge up of G levels: T_n -> T_{n+G} ----------------------------------------
 
@@ -339,8 +394,8 @@ __device__ __forceinline__ void load_tn(const TS *T, TS *lds, int N, int n, int 
 // columns of T_n below it.  Levels alternate between two LDS regions.  Every
 // level with a destination in a.T is stored (the last one always).
 template <typename TS, int G> struct FuseUp {
-    static constexpr int L = 128, V = sizeof(TS) == 16 ? 1 : 2, H = L / (64 * V);
-    static constexpr int NT = G == 4 ? 1024 : G == 3 ? 512 : 256, NW = NT / 64;
+    static constexpr int L = kWindow, V = sizeof(TS) == 16 ? 1 : 2, H = L / (64 * V);
+    static constexpr int NT = G == 2 ? 256 : G == 3 || sizeof(TS) == 4 ? 512 : 1024, NW = NT / 64;
     static constexpr int win = L - (2 << G);  // 2 (2^G - 1) rows of halo
     static constexpr int rows(int j) { return (1 << (G - j)) * ((1 << j) + 1); }
     static constexpr int region(int p) {
@@ -351,7 +406,7 @@ template <typename TS, int G> struct FuseUp {
     static constexpr int lds = ((region(0) + region(1)) * L + kFusePad) * (int)sizeof(TS);
 };
 
-template <typename TS, int G, int j>
+template <typename TS, int G, int j, bool IN>
 __device__ __forceinline__ void fuse_up_level(const FuseArgs &a, const FuseTile &t, char *lds,
                                               int own, int sb, int tid) {
     using F = FuseUp<TS, G>;
@@ -367,20 +422,20 @@ __device__ __forceinline__ void fuse_up_level(const FuseArgs &a, const FuseTile 
     // the last direction is the next cone's first: stored by the last cone only
     const bool last = t.ii == (1 << a.n) - 1;
     for (int i = wave; i < cols * pdirs * H; i += NW) {
-        const int h = i % H, e = i / H, X = j == G ? 0 : e / pdirs, k = j == G ? e : e % pdirs;
+        const int h = i % H, e = i / H, X = e & (cols - 1), k = e >> (G - j);
         const bool two = k + 1 < pdirs;  // direction 2k + 1 as well
         const Rows<V> w((h * 64 + lane) * V, t.y0, sb, S);
         const int y = w.y(X << j);
         C ev[V], od[V];
-        fused_up<TS, V, L, true>(src + (2 * X * pdirs + k) * L + w.r, pdirs * L, k, w,
-                                 y + (sb << (j - 1)), ev, od);
+        fused_up<TS, V, L, true, IN>(src + (2 * X * pdirs + k) * L + w.r, pdirs * L, k, w,
+                                     y + (sb << (j - 1)), ev, od);
         if constexpr (j < G) {
             TS *d = dst + (X * dirs + 2 * k) * L + w.r;
             st_row<V>(d, ev);
             if (two) st_row<V>(d + L, od);
         }
         if ((j == G || out) && w.r < own) {
-            TS *o = out + ((unsigned)t.q * t_entries(N, m) +
+            TS *o = out + ((unsigned)t.q * a.te[j] +
                            ((unsigned)(((t.x << (G - j)) + X) * ((1 << m) + 1) + (t.ii << j) + 2 * k)
                             << N));
             if (two || last) st_row<V>(o + (unsigned)y, ev);
@@ -389,29 +444,37 @@ __device__ __forceinline__ void fuse_up_level(const FuseArgs &a, const FuseTile 
     }
 }
 
-template <typename TS, int G>
-__device__ __forceinline__ void fuse_up_block(const FuseArgs &a, unsigned tile, char *lds, int tid) {
-    using F = FuseUp<TS, G>;
-    const int N = a.N, S = 1 << N, n = a.n;
-    const FuseTile t = fuse_tile(a, tile);
-    const int sb = 2 * t.ii - (1 << n);
-    const int own = a.win < S - t.y0 ? a.win : S - t.y0;
-    load_tn<TS, F::V, F::L, F::NT, (1 << G)>(
-        reinterpret_cast<const TS *>(a.T[0]) + (unsigned)t.q * t_entries(N, n),
-        reinterpret_cast<TS *>(lds), N, n, t.ii, t.x << G, t.x << G, t.y0, sb, tid,
-        [](int i) { return i; });
+template <typename TS, int G, bool IN>
+__device__ __forceinline__ void fuse_up_levels(const FuseArgs &a, const FuseTile &t, char *lds,
+                                               int own, int sb, int tid) {
+    fuse_up_level<TS, G, 1, IN>(a, t, lds, own, sb, tid);
     __syncthreads();
-    fuse_up_level<TS, G, 1>(a, t, lds, own, sb, tid);
-    __syncthreads();
-    fuse_up_level<TS, G, 2>(a, t, lds, own, sb, tid);
+    fuse_up_level<TS, G, 2, IN>(a, t, lds, own, sb, tid);
     if constexpr (G >= 3) {
         __syncthreads();
-        fuse_up_level<TS, G, 3>(a, t, lds, own, sb, tid);
+        fuse_up_level<TS, G, 3, IN>(a, t, lds, own, sb, tid);
     }
     if constexpr (G >= 4) {
         __syncthreads();
-        fuse_up_level<TS, G, 4>(a, t, lds, own, sb, tid);
+        fuse_up_level<TS, G, 4, IN>(a, t, lds, own, sb, tid);
     }
+}
+
+template <typename TS, int G>
+__device__ __forceinline__ void fuse_up_block(const FuseArgs &a, char *lds, int tid) {
+    using F = FuseUp<TS, G>;
+    const int N = a.N, S = 1 << N, n = a.n;
+    const FuseTile t = fuse_tile(a);
+    const int sb = 2 * t.ii - (1 << n);
+    const int own = a.win < S - t.y0 ? a.win : S - t.y0;
+    const int wave = __builtin_amdgcn_readfirstlane(tid >> 6), lane = tid & 63;
+    TnLoad<TS, F::V, F::L, F::NT, (1 << G)> ld;
+    ld.load(reinterpret_cast<const TS *>(a.T[0]) + (unsigned)t.q * a.te[0], N, n, t.ii, t.x << G, t.y0,
+            sb, wave, lane);
+    ld.store(reinterpret_cast<TS *>(lds), wave, lane, [](int i) { return i; });
+    __syncthreads();
+    if (window_inside(t.y0, (1 << G) - 1, sb, S)) fuse_up_levels<TS, G, true>(a, t, lds, own, sb, tid);
+    else fuse_up_levels<TS, G, false>(a, t, lds, own, sb, tid);
 }
 
 // ---- the top M levels: T_n -> R_n, n = N - M -------------------------------------
@@ -421,9 +484,9 @@ __device__ __forceinline__ void fuse_up_block(const FuseArgs &a, unsigned tile, 
 // they fit, those lie over T_n's even columns, which only the merge up of
 // T_{n+1} reads (T_n's odd columns come first in LDS).
 template <typename TS, int M> struct FuseTop {
-    static constexpr int L = 128, ch = Store<TS>::ch;
+    static constexpr int L = kWindow, ch = Store<TS>::ch;
     static constexpr int V = sizeof(TS) == 16 ? 1 : 2, H = L / (64 * V);
-    static constexpr int NT = M >= 4 ? 1024 : 512, NW = NT / 64;
+    static constexpr int NT = M == 4 && sizeof(TS) == 8 ? 1024 : 512, NW = NT / 64;
     static constexpr int win = L - 2 * ((1 << M) - 1);  // halo: from column 1 to the far edge
     static constexpr int cols(int j) { return (1 << (M - j)) - 1; }
     static constexpr int t_rows(int j) { return cols(j) * ((1 << j) + 1); }
@@ -463,7 +526,7 @@ template <typename TS, int M, int j> __device__ __forceinline__ float *top_r(cha
            (((j & 1) ? F::r_region(0) : 0) + (x - 1) * (1 << j) * F::ch) * F::L;
 }
 
-template <typename TS, int M, int j>
+template <typename TS, int M, int j, bool IN>
 __device__ __forceinline__ void fuse_top_up(const FuseArgs &a, const FuseTile &t, char *lds, int own,
                                             int sb, int tid) {
     using F = FuseTop<TS, M>;
@@ -481,13 +544,13 @@ __device__ __forceinline__ void fuse_top_up(const FuseArgs &a, const FuseTile &t
         // T_n's odd columns lie first, so its far column is 2^(M-1) - 1 columns back
         constexpr int far = j == 1 ? (1 - (1 << (M - 1))) * 2 * L : pdirs * L;
         C ev[V], od[V];
-        fused_up<TS, V, L, true>(top_t<TS, M, j - 1>(lds, 2 * X) + k * L + w.r, far, k, w,
-                                 y + (sb << (j - 1)), ev, od);
+        fused_up<TS, V, L, true, IN>(top_t<TS, M, j - 1>(lds, 2 * X) + k * L + w.r, far, k, w,
+                                     y + (sb << (j - 1)), ev, od);
         TS *d = top_t<TS, M, j>(lds, X) + 2 * k * L + w.r;
         st_row<V>(d, ev);
         if (two) st_row<V>(d + L, od);
         if (out && w.r < own) {
-            TS *o = out + ((unsigned)t.q * t_entries(N, m) +
+            TS *o = out + ((unsigned)t.q * a.te[j] +
                            ((unsigned)(X * ((1 << m) + 1) + (t.ii << j) + 2 * k) << N));
             if (two || last) st_row<V>(o + (unsigned)y, ev);
             if (two) st_row<V>(o + (unsigned)(y + S), od);
@@ -495,7 +558,7 @@ __device__ __forceinline__ void fuse_top_up(const FuseArgs &a, const FuseTile &t
     }
 }
 
-template <typename TS, int M, int j>
+template <typename TS, int M, int j, bool IN>
 __device__ __forceinline__ void fuse_top_down(const FuseArgs &a, const FuseTile &t, char *lds,
                                               int own, int sb, int tid) {
     using F = FuseTop<TS, M>;
@@ -514,12 +577,11 @@ __device__ __forceinline__ void fuse_top_down(const FuseArgs &a, const FuseTile 
         float o[CH][V];
         if (x & 1) {
             const TS *tb = top_t<TS, M, j>(lds, x) + k * L + w.r;
-            const int yv = y + (sb << j);
             if constexpr (j + 1 < M) {
                 // a probe past the last column is the light from beyond the grid
                 const int c = (x + 1) >> 1, cc = c <= F::cols(j + 1) ? c : c - 1;
                 const float *rm = top_r<TS, M, j + 1>(lds, cc > 0 ? cc : 1) + (2 * CH * L + 2) * k + w.r;
-                fused_down_odd<TS, V, L>(tb, rm, c <= F::cols(j + 1), k, wt, w, yv, o);
+                fused_down_odd<TS, V, L, IN>(tb, rm, c <= F::cols(j + 1), k, wt, w, y + (sb << j), o);
             } else {
                 // R_N is the light from beyond the grid
                 C tv[2][V];
@@ -529,8 +591,7 @@ __device__ __forceinline__ void fuse_top_down(const FuseArgs &a, const FuseTile 
                 for (int c = 0; c < CH; ++c)
 #pragma unroll
                     for (int v = 0; v < V; ++v) {
-                        o[c][v] = 0.f;
-                        o[c][v] += fmaf(trans(tv[0][v]), wt.y, wt.x * rad(tv[0][v], c));
+                        o[c][v] = fmaf(trans(tv[0][v]), wt.y, wt.x * rad(tv[0][v], c));
                         o[c][v] += fmaf(trans(tv[1][v]), wt.w, wt.z * rad(tv[1][v], c));
                     }
             }
@@ -544,7 +605,7 @@ __device__ __forceinline__ void fuse_top_down(const FuseArgs &a, const FuseTile 
                     ld_row<V>(top_t<TS, M, j + 1>(lds, cc) + 2 * (k + up) * L + w.r, ed[up]);
                 const float *rn = top_r<TS, M, j + 1>(lds, cc) + 2 * CH * L * k + w.r;
                 const float *rf = rn + (far ? (2 << j) * CH * L : 0) + 4 * k;
-                fused_down_even<TS, V, L>(ed, rn, rf, far, k, wt, w, y + 2 * (sb << j), o);
+                fused_down_even<TS, V, L, IN>(ed, rn, rf, far, k, wt, w, y + 2 * (sb << j), o);
             }
         }
         if constexpr (j > 0) {
@@ -561,39 +622,48 @@ __device__ __forceinline__ void fuse_top_down(const FuseArgs &a, const FuseTile 
     }
 }
 
-template <typename TS, int M>
-__device__ __forceinline__ void fuse_top_block(const FuseArgs &a, unsigned tile, char *lds, int tid) {
-    using F = FuseTop<TS, M>;
-    const int N = a.N, S = 1 << N, n = a.n;
-    const FuseTile t = fuse_tile(a, tile);
-    const int sb = 2 * t.ii - (1 << n);
-    const int own = a.win < S - t.y0 ? a.win : S - t.y0;
-    load_weights<M>(reinterpret_cast<float4 *>(lds + F::w_off), n, t.ii,
-                    a.env ? a.env + (size_t)(a.q0 + t.q) * kConeTable : nullptr, tid);
-    load_tn<TS, F::V, F::L, F::NT, F::cols(0)>(
-        reinterpret_cast<const TS *>(a.T[0]) + (unsigned)t.q * t_entries(N, n),
-        reinterpret_cast<TS *>(lds), N, n, t.ii, 1, 1, t.y0, sb, tid,
-        [](int i) { return F::slot(i + 1); });
-    __syncthreads();
-    fuse_top_up<TS, M, 1>(a, t, lds, own, sb, tid);
+template <typename TS, int M, bool IN>
+__device__ __forceinline__ void fuse_top_levels(const FuseArgs &a, const FuseTile &t, char *lds,
+                                                int own, int sb, int tid) {
+    fuse_top_up<TS, M, 1, IN>(a, t, lds, own, sb, tid);
     __syncthreads();
     if constexpr (M >= 3) {
-        fuse_top_up<TS, M, 2>(a, t, lds, own, sb, tid);
+        fuse_top_up<TS, M, 2, IN>(a, t, lds, own, sb, tid);
         __syncthreads();
     }
     if constexpr (M >= 4) {
-        fuse_top_up<TS, M, 3>(a, t, lds, own, sb, tid);
+        fuse_top_up<TS, M, 3, IN>(a, t, lds, own, sb, tid);
         __syncthreads();
-        fuse_top_down<TS, M, 3>(a, t, lds, own, sb, tid);
+        fuse_top_down<TS, M, 3, IN>(a, t, lds, own, sb, tid);
         __syncthreads();
     }
     if constexpr (M >= 3) {
-        fuse_top_down<TS, M, 2>(a, t, lds, own, sb, tid);
+        fuse_top_down<TS, M, 2, IN>(a, t, lds, own, sb, tid);
         __syncthreads();
     }
-    fuse_top_down<TS, M, 1>(a, t, lds, own, sb, tid);
+    fuse_top_down<TS, M, 1, IN>(a, t, lds, own, sb, tid);
     __syncthreads();
-    fuse_top_down<TS, M, 0>(a, t, lds, own, sb, tid);
+    fuse_top_down<TS, M, 0, IN>(a, t, lds, own, sb, tid);
+}
+
+template <typename TS, int M>
+__device__ __forceinline__ void fuse_top_block(const FuseArgs &a, char *lds, int tid) {
+    using F = FuseTop<TS, M>;
+    const int N = a.N, S = 1 << N, n = a.n;
+    const FuseTile t = fuse_tile(a);
+    const int sb = 2 * t.ii - (1 << n);
+    const int own = a.win < S - t.y0 ? a.win : S - t.y0;
+    const int wave = __builtin_amdgcn_readfirstlane(tid >> 6), lane = tid & 63;
+    TnLoad<TS, F::V, F::L, F::NT, F::cols(0)> ld;
+    ld.load(reinterpret_cast<const TS *>(a.T[0]) + (unsigned)t.q * a.te[0], N, n, t.ii, 1, t.y0, sb, wave,
+            lane);
+    const float4 wt = load_weight<M>(
+        n, t.ii, a.env ? a.env + (size_t)(a.q0 + t.q) * kConeTable : nullptr, tid);
+    ld.store(reinterpret_cast<TS *>(lds), wave, lane, [](int i) { return F::slot(i + 1); });
+    if (tid < (1 << M) - 1) reinterpret_cast<float4 *>(lds + F::w_off)[tid] = wt;
+    __syncthreads();
+    if (window_inside(t.y0, (1 << M) - 2, sb, S)) fuse_top_levels<TS, M, true>(a, t, lds, own, sb, tid);
+    else fuse_top_levels<TS, M, false>(a, t, lds, own, sb, tid);
 }
 
 // ---- merge down of two levels: (T_n, R_{n+2}) -> R_n, n >= 2 -------------------------
@@ -601,11 +671,12 @@ __device__ __forceinline__ void fuse_top_block(const FuseArgs &a, unsigned tile,
 // A block computes R_n at the columns x0 + 1 .. x0 + CC (x0 a multiple of CC) of
 // one cone: these read columns 1 .. CC/2 + 1 (from x0/2) of R_{n+1} and 1 ..
 // CC/4 + 1 (from x0/4) of R_{n+2}; T_{n+1}, and the even directions of
-// T_{n+2}, are rebuilt from T_n's columns x0 + 1 .. x0 + CC + 3.  R_{n+1} lies
-// over the columns of T_n that only the rebuild reads.
+// T_{n+2}, are rebuilt from T_n's columns x0 + 1 .. x0 + CC + 3.  R_{n+2} and
+// R_{n+1} lie over the columns of T_n that only the rebuild reads, where they fit
+// (R_{n+2} waits for its place in registers).
 template <typename TS> struct FuseDown {
-    static constexpr int L = 128, V = sizeof(TS) == 16 ? 1 : 2, H = L / (64 * V);
-    static constexpr int NT = 512, NW = NT / 64, ch = Store<TS>::ch;
+    static constexpr int L = kWindow, V = sizeof(TS) == 16 ? 1 : 2, H = L / (64 * V);
+    static constexpr int NT = 256, NW = NT / 64, ch = Store<TS>::ch;
     static constexpr int CC = sizeof(TS) == 16 ? 4 : 8;
     static constexpr int win = L - 2 * (CC + 3);
     static constexpr int c0 = CC + 3, c1 = CC / 2 + 1, c2 = CC / 4 + 1;  // columns per level
@@ -613,10 +684,11 @@ template <typename TS> struct FuseDown {
     static constexpr int odd_bytes = (CC / 2) * 2 * L * (int)sizeof(TS);
     static constexpr int t_bytes = (t0_rows + t1_rows) * L * (int)sizeof(TS);
     static constexpr int r2_bytes = c2 * 4 * ch * L * 4, r1_bytes = c1 * 2 * ch * L * 4;
-    static constexpr bool overlay = t0_rows * L * (int)sizeof(TS) - odd_bytes >= r1_bytes;
-    static constexpr int r1_off = overlay ? odd_bytes : t_bytes + r2_bytes;
+    static constexpr bool overlay =
+        t0_rows * L * (int)sizeof(TS) - odd_bytes >= r1_bytes + r2_bytes;
+    static constexpr int r1_off = overlay ? odd_bytes : t_bytes, r2_off = r1_off + r1_bytes;
     static constexpr int w_off =
-        t_bytes + r2_bytes + (overlay ? 0 : r1_bytes) + kFusePad * (int)sizeof(TS);
+        t_bytes + (overlay ? 0 : r1_bytes + r2_bytes) + kFusePad * (int)sizeof(TS);
     static constexpr int lds = w_off + 16 * 3;
     // LDS column of T_n's column x0 + i: the odd ones below CC first, then the
     // rest in order
@@ -625,69 +697,74 @@ template <typename TS> struct FuseDown {
     }
 };
 
-template <typename TS>
-__device__ __forceinline__ void fuse_down_block(const FuseArgs &a, unsigned tile, char *lds, int tid) {
+// R_{n+2} of the block's window: into registers, later into LDS (as TnLoad).
+template <typename TS> struct R2Load {
+    using F = FuseDown<TS>;
+    static constexpr int V = F::V, H = F::H, CH = F::ch, ROWS = F::c2 * 4 * CH * H;
+    static constexpr int IT = (ROWS + F::NW - 1) / F::NW;
+    using Raw = typename RawVec<4 * V>::type;
+    Raw v[IT];
+    __device__ __forceinline__ static int row(int it, int wave) {
+        const int i = it * F::NW + wave;
+        return (it + 1) * F::NW <= ROWS ? i : i < ROWS ? i : ROWS - 1;
+    }
+    __device__ __forceinline__ void load(const FuseArgs &a, const FuseTile &t, int sb, int wave, int lane) {
+        const int N = a.N, S = 1 << N, n = a.n, x0 = t.x * F::CC, last = (S >> (n + 2)) - 1;
+        const size_t plane = (size_t)a.nq << (2 * N);
+        const float *R2 = a.R[2] + ((unsigned)t.q << (2 * N));
+#pragma unroll
+        for (int it = 0; it < IT; ++it) {
+            const int i = row(it, wave), h = i % H, e = i / H, pl = e % CH, k = (e / CH) & 3;
+            const int c = 1 + e / (4 * CH), X = (x0 >> 2) + c;
+            const Rows<V> w((h * 64 + lane) * V, t.y0, sb, S);
+            v[it] = *reinterpret_cast<const Raw *>(
+                R2 + pl * plane +
+                (((unsigned)(((X < last ? X : last) << (n + 2)) | (4 * t.ii + k)) << N) +
+                 (unsigned)w.y(4 * c - 1)));
+        }
+    }
+    __device__ __forceinline__ void store(float *r2, int wave, int lane) const {
+#pragma unroll
+        for (int it = 0; it < IT; ++it) {
+            const int i = row(it, wave);
+            *reinterpret_cast<Raw *>(r2 + (i / H) * F::L + ((i % H) * 64 + lane) * V) = v[it];
+        }
+    }
+};
+
+template <typename TS, bool IN>
+__device__ __forceinline__ void fuse_down_levels(const FuseArgs &a, const FuseTile &t, char *lds,
+                                                 const R2Load<TS> &rl, int own, int sb, int tid) {
     using F = FuseDown<TS>;
     using C = typename Store<TS>::C;
     constexpr int V = F::V, L = F::L, H = F::H, NW = F::NW, CH = F::ch, CC = F::CC;
-    const int N = a.N, S = 1 << N, n = a.n;
-    const FuseTile t = fuse_tile(a, tile);
-    const int x0 = t.x * CC, cols = S >> n;
-    const int sb = 2 * t.ii - (1 << n);
-    const int own = a.win < S - t.y0 ? a.win : S - t.y0;
+    const int N = a.N, S = 1 << N, n = a.n, x0 = t.x * CC, cols = S >> n;
     const size_t plane = (size_t)a.nq << (2 * N);
     const int wave = __builtin_amdgcn_readfirstlane(tid >> 6), lane = tid & 63;
     TS *t0 = reinterpret_cast<TS *>(lds), *t1 = t0 + F::t0_rows * L;
-    float *r2 = reinterpret_cast<float *>(lds + F::t_bytes);
+    float *r2 = reinterpret_cast<float *>(lds + F::r2_off);
     float *r1 = reinterpret_cast<float *>(lds + F::r1_off);
-    float4 *wl = reinterpret_cast<float4 *>(lds + F::w_off);
+    const float4 *wl = reinterpret_cast<const float4 *>(lds + F::w_off);
     auto t0_col = [&](int i) { return t0 + F::slot(i) * 2 * L; };
     auto t1_col = [&](int i) { return t1 + (i - 1) * 3 * L; };
     auto r2_col = [&](int i) { return r2 + (i - 1) * 4 * CH * L; };
     auto r1_col = [&](int i) { return r1 + (i - 1) * 2 * CH * L; };
-    load_weights<2>(wl, n, t.ii, a.env ? a.env + (size_t)(a.q0 + t.q) * kConeTable : nullptr, tid);
-    // R_{n+2} into LDS (its loads in flight with T_n's)
-    {
-        constexpr int ROWS = F::c2 * 4 * CH * H, IT = (ROWS + NW - 1) / NW;
-        using Raw = typename RawVec<4 * V>::type;
-        Raw v[IT];
-        const float *R2 = a.R[2] + ((unsigned)t.q << (2 * N));
-#pragma unroll
-        for (int it = 0; it < IT; ++it) {
-            const int i = it * NW + wave;
-            if (i < ROWS) {
-                const int h = i % H, e = i / H, pl = e % CH, k = (e / CH) & 3, c = 1 + e / (4 * CH);
-                const Rows<V> w((h * 64 + lane) * V, t.y0, sb, S);
-                const int X = (x0 >> 2) + c, last = (cols >> 2) - 1;
-                v[it] = *reinterpret_cast<const Raw *>(
-                    R2 + pl * plane +
-                    (((unsigned)(((X < last ? X : last) << (n + 2)) | (4 * t.ii + k)) << N) +
-                     (unsigned)w.y(4 * c - 1)));
-            }
-        }
-        load_tn<TS, V, L, F::NT, F::c0>(
-            reinterpret_cast<const TS *>(a.T[0]) + (unsigned)t.q * t_entries(N, n), t0, N, n, t.ii,
-            x0 + 1, x0 + 1, t.y0, sb, tid, [](int i) { return F::slot(i + 1); });
-#pragma unroll
-        for (int it = 0; it < IT; ++it) {
-            const int i = it * NW + wave;
-            if (i < ROWS)
-                *reinterpret_cast<Raw *>(r2 + (i / H) * L + ((i % H) * 64 + lane) * V) = v[it];
-        }
-    }
-    __syncthreads();
     // T_{n+1}: directions 0, 1 and direction 2 of every column
     for (int i = wave; i < F::c1 * 2 * H; i += NW) {
         const int h = i % H, e = i / H, X = 1 + (e >> 1), k = e & 1;
         const Rows<V> w((h * 64 + lane) * V, t.y0, sb, S);
         const int far = (int)(t0_col(2 * X + 1) - t0_col(2 * X));
         C ev[V], od[V];
-        fused_up<TS, V, L, true>(t0_col(2 * X) + k * L + w.r, far, k, w, w.y(2 * X - 1) + sb, ev, od);
+        fused_up<TS, V, L, true, IN>(t0_col(2 * X) + k * L + w.r, far, k, w, w.y(2 * X - 1) + sb, ev, od);
         TS *d = t1_col(X) + 2 * k * L + w.r;
         st_row<V>(d, ev);
         if (k == 0) st_row<V>(d + L, od);
     }
     __syncthreads();
+    if constexpr (F::overlay) {
+        rl.store(r2, wave, lane);
+        __syncthreads();
+    }
     // R_{n+1}
     for (int i = wave; i < F::c1 * 2 * H; i += NW) {
         const int h = i % H, e = i / H, x = 1 + (e >> 1), k = e & 1;
@@ -698,21 +775,21 @@ __device__ __forceinline__ void fuse_down_block(const FuseArgs &a, unsigned tile
         const int c = (x + 1) >> 1;
         float o[CH][V];
         if (x & 1) {
-            fused_down_odd<TS, V, L>(t1_col(x) + k * L + w.r, r2_col(c) + (2 * CH * L + 2) * k + w.r,
-                                     (x0 >> 2) + c < (cols >> 2), k, wt, w, y + 2 * sb, o);
+            fused_down_odd<TS, V, L, IN>(t1_col(x) + k * L + w.r, r2_col(c) + (2 * CH * L + 2) * k + w.r,
+                                         (x0 >> 2) + c < (cols >> 2), k, wt, w, y + 2 * sb, o);
         } else {
             const int cc = x >> 1;
             C ed[2][V], none[V];
 #pragma unroll
             for (int up = 0; up < 2; ++up) {
-                fused_up<TS, V, L, false>(t1_col(2 * cc) + (k + up) * L + w.r, 3 * L, k + up, w,
-                                          y + 2 * sb, ed[up], none);
+                fused_up<TS, V, L, false, IN>(t1_col(2 * cc) + (k + up) * L + w.r, 3 * L, k + up, w,
+                                              y + 2 * sb, ed[up], none);
 #pragma unroll
                 for (int j = 0; j < V; ++j) ed[up][j] = stored(ed[up][j], static_cast<const TS *>(nullptr));
             }
             const float *rn = r2_col(cc) + 2 * CH * L * k + w.r;
-            fused_down_even<TS, V, L>(ed, rn, rn + 4 * CH * L + 4 * k, (x0 >> 2) + cc + 1 < (cols >> 2),
-                                      k, wt, w, y + 4 * sb, o);
+            fused_down_even<TS, V, L, IN>(ed, rn, rn + 4 * CH * L + 4 * k,
+                                          (x0 >> 2) + cc + 1 < (cols >> 2), k, wt, w, y + 4 * sb, o);
         }
         float *dst = r1_col(x) + k * CH * L + w.r;
 #pragma unroll
@@ -735,16 +812,16 @@ __device__ __forceinline__ void fuse_down_block(const FuseArgs &a, unsigned tile
         const int c = (x + 1) >> 1;
         float o[CH][V];
         if (x & 1) {
-            fused_down_odd<TS, V, L>(t0_col(x) + w.r, r1_col(c) + w.r, (x0 >> 1) + c < (cols >> 1), 0,
-                                     wt, w, y + sb, o);
+            fused_down_odd<TS, V, L, IN>(t0_col(x) + w.r, r1_col(c) + w.r, (x0 >> 1) + c < (cols >> 1),
+                                         0, wt, w, y + sb, o);
         } else {
             const int cc = x >> 1;
             C ed[2][V];
 #pragma unroll
             for (int up = 0; up < 2; ++up) ld_row<V>(t1_col(cc) + 2 * up * L + w.r, ed[up]);
             const float *rn = r1_col(cc) + w.r;
-            fused_down_even<TS, V, L>(ed, rn, rn + 2 * CH * L, (x0 >> 1) + cc + 1 < (cols >> 1), 0, wt,
-                                      w, y + 2 * sb, o);
+            fused_down_even<TS, V, L, IN>(ed, rn, rn + 2 * CH * L, (x0 >> 1) + cc + 1 < (cols >> 1), 0,
+                                          wt, w, y + 2 * sb, o);
         }
         if (w.r < own) {
             float *out = a.R[0] + (((unsigned)t.q << (2 * N)) +
@@ -753,4 +830,31 @@ __device__ __forceinline__ void fuse_down_block(const FuseArgs &a, unsigned tile
             for (int c2 = 0; c2 < CH; ++c2) st_f<V>(out + c2 * plane + (unsigned)y, o[c2]);
         }
     }
+}
+
+template <typename TS>
+__device__ __forceinline__ void fuse_down_block(const FuseArgs &a, char *lds, int tid) {
+    using F = FuseDown<TS>;
+    constexpr int V = F::V, L = F::L, CC = F::CC;
+    const int N = a.N, S = 1 << N, n = a.n;
+    const FuseTile t = fuse_tile(a);
+    const int x0 = t.x * CC;
+    const int sb = 2 * t.ii - (1 << n);
+    const int own = a.win < S - t.y0 ? a.win : S - t.y0;
+    const int wave = __builtin_amdgcn_readfirstlane(tid >> 6), lane = tid & 63;
+    TS *t0 = reinterpret_cast<TS *>(lds);
+    float4 *wl = reinterpret_cast<float4 *>(lds + F::w_off);
+    TnLoad<TS, V, L, F::NT, F::c0> ld;
+    ld.load(reinterpret_cast<const TS *>(a.T[0]) + (unsigned)t.q * a.te[0], N, n, t.ii, x0 + 1, t.y0, sb,
+            wave, lane);
+    R2Load<TS> rl;
+    rl.load(a, t, sb, wave, lane);
+    const float4 wt = load_weight<2>(
+        n, t.ii, a.env ? a.env + (size_t)(a.q0 + t.q) * kConeTable : nullptr, tid);
+    ld.store(t0, wave, lane, [](int i) { return F::slot(i + 1); });
+    if constexpr (!F::overlay) rl.store(reinterpret_cast<float *>(lds + F::r2_off), wave, lane);
+    if (tid < 3) wl[tid] = wt;
+    __syncthreads();
+    if (window_inside(t.y0, CC + 3, sb, S)) fuse_down_levels<TS, true>(a, t, lds, rl, own, sb, tid);
+    else fuse_down_levels<TS, false>(a, t, lds, rl, own, sb, tid);
 }

@@ -153,8 +153,13 @@ struct FuseArgs {
     float *R[4];
     const float *env;  // environment table (nullable)
     int N, n, levels, nq, q0;
-    int win, nwin;     // rows of a window that are stored, windows over the grid
-    int chunks;        // column chunks
+    // set by size_fused: rows of a window that are stored and windows over the
+    // grid (and ceil(2^32 / nwin), 0 for one window); log2 of the column chunks; an eighth of the
+    // tiles (0: not a multiple of eight); entries per quadrant of T_{n+j}
+    int win, nwin;
+    unsigned inv_nwin;
+    int lchunks, eighth;
+    unsigned te[5];
     int half, rgb;     // interval storage
 };
 

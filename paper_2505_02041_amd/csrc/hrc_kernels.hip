@@ -2722,18 +2722,17 @@ __global__ __launch_bounds__(256) void hrc_gather_adj(Phase p) {
 template <typename TS, int G>
 __global__ __launch_bounds__((FuseUp<TS, G>::NT)) void hrc_fuse_up(Phase p) {
     __shared__ __align__(16) char lds[FuseUp<TS, G>::lds];
-    fuse_up_block<TS, G>(p.a.fu, xcd_tile_blk(blockIdx.x, gridDim.x, p.xblk), lds, (int)threadIdx.x);
+    fuse_up_block<TS, G>(p.a.fu, lds, (int)threadIdx.x);
 }
 template <typename TS, int M>
 __global__ __launch_bounds__((FuseTop<TS, M>::NT)) void hrc_fuse_top(Phase p) {
     __shared__ __align__(16) char lds[FuseTop<TS, M>::lds];
-    fuse_top_block<TS, M>(p.a.fu, xcd_tile_blk(blockIdx.x, gridDim.x, p.xblk), lds,
-                             (int)threadIdx.x);
+    fuse_top_block<TS, M>(p.a.fu, lds, (int)threadIdx.x);
 }
 template <typename TS>
 __global__ __launch_bounds__(FuseDown<TS>::NT) void hrc_fuse_down(Phase p) {
     __shared__ __align__(16) char lds[FuseDown<TS>::lds];
-    fuse_down_block<TS>(p.a.fu, xcd_tile_blk(blockIdx.x, gridDim.x, p.xblk), lds, (int)threadIdx.x);
+    fuse_down_block<TS>(p.a.fu, lds, (int)threadIdx.x);
 }
 
 // Kernel, block size and window of a fused phase.
@@ -3008,18 +3007,24 @@ void size_fused(Phase &p) {
     const int S = 1 << a.N;
     a.nwin = (S + f.win - 1) / f.win;
     a.win = (S / 2 + a.nwin - 1) / a.nwin * 2;  // even, the windows of equal size
+    // exact for every tile (fewer than 2^32 / nwin of them)
+    a.inv_nwin = a.nwin == 1 ? 0u : (unsigned)((0x100000000ull + a.nwin - 1) / (unsigned)a.nwin);
     if (p.kind == PH_FUSE_UP)
-        a.chunks = S >> (a.n + a.levels);
+        a.lchunks = a.N - a.n - a.levels;
     else if (p.kind == PH_FUSE_DOWN)
-        a.chunks = (S >> a.n) / (a.rgb && !a.half ? FuseDown<float4>::CC : FuseDown<float2>::CC);
+        a.lchunks = a.N - a.n - (a.rgb && !a.half ? 2 : 3);  // FuseDown::CC columns
     else
-        a.chunks = 1;
+        a.lchunks = 0;
+    for (int j = 0; j < 5; ++j)
+        a.te[j] = a.n + j <= a.N ? (unsigned)t_level_entries(a.N, a.n + j) : 0;
+    const unsigned tiles = phase_tiles(p);
+    a.eighth = tiles % 8 == 0 ? (int)(tiles / 8) : 0;
 }
 
 unsigned phase_tiles(const Phase &p) {
     if (is_fused(p)) {
         const FuseArgs &a = p.a.fu;
-        return (unsigned)a.nq * (unsigned)a.chunks * ((unsigned)a.nwin << a.n);
+        return (unsigned)a.nq * (((unsigned)a.nwin << a.n) << a.lchunks);
     }
     auto cdiv = [](size_t a, size_t b) { return (unsigned)((a + b - 1) / b); };
     const int N = [&] {
