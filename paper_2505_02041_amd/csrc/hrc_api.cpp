@@ -148,7 +148,9 @@ static int pick_u(const int *U, int kind) { return U ? (U[kind] > 0 ? U[kind] : 
 // forward 2-7%, the RGB forward 4% and the reverse 3-9% faster at 1024^2 ..
 // 4096^2; the same results, since only the order of the tiles changes.
 static int tile_order(int N, int kind) {
-    if (kind == PH_FUSE_UP || kind == PH_FUSE_TOP || kind == PH_FUSE_DOWN) return 0;
+    if (kind == PH_FUSE_UP || kind == PH_FUSE_TOP || kind == PH_FUSE_DOWN ||
+        kind == PH_FUSE_DR)
+        return 0;
     if (N < 10) return 0;
     switch (kind) {
         case PH_UP:
@@ -253,6 +255,27 @@ static int build_fused_merges(const Ws &w, const SolveBuffers &b, bool keep, boo
     return cur;
 }
 
+// Two levels of the merge-down adjoint in one kernel: (T_n, dR_n) -> dR_{n+1},
+// dR_{n+2}.  It rebuilds T_{n+1} from T_n, so n >= 2 (the traced levels are no
+// merges of each other); a level left over is a pass of its own.
+static bool dr_pair(int N, int n) { return n >= kTracedLevels - 1 && n + 2 <= N - 1; }
+static Phase fused_dr_phase(const Ws &w, int N, int n, int half, bool rgb) {
+    Phase p;
+    p.kind = PH_FUSE_DR;
+    FuseArgs f{};
+    f.N = N;
+    f.n = n;
+    f.levels = 2;
+    f.nq = kQuadrants;
+    f.half = half;
+    f.rgb = rgb ? 1 : 0;
+    f.T[0] = w.T(n);
+    for (int j = 0; j < 3; ++j) f.R[j] = w.dR(n + j);
+    p.a.fu = f;
+    size_fused(p);
+    return p;
+}
+
 int build_solve_phases(const Ws &w, const SolveBuffers &b, bool keep_all_r, const int *U,
                        Phase *out, int max_out, bool recompute, bool fused) {
     const int N = w.L.N;
@@ -346,6 +369,10 @@ int build_solve_phases(const Ws &w, const SolveBuffers &b, bool keep_all_r, cons
         p.a.ga = GatherAdjArgs{dgathered, w.dR(0), N};
         add(p);
         for (int n = 0; n + 1 < N; ++n) {
+            if (fused && dr_pair(N, n)) {
+                add(fused_dr_phase(w, N, n++, b.half, false));
+                continue;
+            }
             p = Phase();
             p.kind = PH_DOWN_ADJ;
             p.U = pick_u(U, PH_DOWN_ADJ);
@@ -474,6 +501,10 @@ int build_rgb_backward_phases(const Ws &w, const SolveBuffers &b, Phase *out, in
             add(p);
         }
         for (int n = 0; n + 1 < N; ++n) {
+            if (dr_pair(N, n)) {
+                add(fused_dr_phase(w, N, n++, b.half, true));
+                continue;
+            }
             p = Phase();
             p.kind = PH_DOWN_ADJ_RGB;
             p.a.da = DownAdjArgs{w.dR(n), w.T(n), w.T(n + 1), w.dR(n + 1), t_level_entries(N, n),
@@ -853,6 +884,10 @@ static int phase_passes(const Phase &p, int *kind, int *level) {
         case PH_FUSE_DOWN:
             add(PH_DOWN, p.a.fu.n + 1);
             add(PH_DOWN, p.a.fu.n);
+            break;
+        case PH_FUSE_DR:
+            add(PH_DOWN_ADJ, p.a.fu.n);
+            add(PH_DOWN_ADJ, p.a.fu.n + 1);
             break;
         default: add(p.kind, -1);
     }

@@ -115,12 +115,14 @@ void phase_access(const Phase &p, std::vector<const void *> &rd, std::vector<con
         }
         case PH_FUSE_UP:
         case PH_FUSE_TOP:
-        case PH_FUSE_DOWN: {
+        case PH_FUSE_DOWN:
+        case PH_FUSE_DR: {
             const FuseArgs &a = p.a.fu;
             r(a.T[0]);
             for (int j = 1; j < 5; ++j) w(a.T[j]);
+            const int read = p.kind == PH_FUSE_DOWN ? 2 : p.kind == PH_FUSE_DR ? 0 : -1;
             for (int j = 0; j < 4; ++j) {
-                if (p.kind == PH_FUSE_DOWN && j == 2) r(a.R[j]);
+                if (j == read) r(a.R[j]);
                 else w(a.R[j]);
             }
             break;

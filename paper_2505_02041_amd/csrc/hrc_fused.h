@@ -678,7 +678,8 @@ template <typename TS> struct FuseDown {
     static constexpr int L = kWindow, V = sizeof(TS) == 16 ? 1 : 2, H = L / (64 * V);
     static constexpr int NT = 256, NW = NT / 64, ch = Store<TS>::ch;
     static constexpr int CC = sizeof(TS) == 16 ? 4 : 8;
-    static constexpr int win = L - 2 * (CC + 3);
+    // R_n looks up to 4 rows into R_{n+1}, that up to 8 into R_{n+2}: six columns on
+    static constexpr int win = L - 12;
     static constexpr int c0 = CC + 3, c1 = CC / 2 + 1, c2 = CC / 4 + 1;  // columns per level
     static constexpr int t0_rows = 2 * c0, t1_rows = 3 * c1;
     static constexpr int odd_bytes = (CC / 2) * 2 * L * (int)sizeof(TS);
@@ -857,4 +858,190 @@ __device__ __forceinline__ void fuse_down_block(const FuseArgs &a, char *lds, in
     __syncthreads();
     if (window_inside(t.y0, CC + 3, sb, S)) fuse_down_levels<TS, true>(a, t, lds, rl, own, sb, tid);
     else fuse_down_levels<TS, false>(a, t, lds, rl, own, sb, tid);
+}
+
+// ---- adjoint of the merge down, two levels: (T_n, dR_n) -> dR_{n+1}, dR_{n+2}, n >= 2 ----
+
+// A block takes one cone ii of level n and the columns x0 .. x0 + CC - 1 (as seen
+// from below): it writes dR_{n+1} at CC/2 columns from x0/2 and dR_{n+2} at CC/4
+// from x0/4.  In gather form these read back along the lower edge: dR_n and
+// T_n's transmittances from column x0 - 6 on, and two columns of dR_{n+1} more
+// than the block writes.  The transmittances of T_{n+1} and T_{n+2} are rebuilt.
+// Lookups run down the window, at most 4 + 8 rows, so the first 12 rows of a
+// window hold no valid results.
+template <typename TS> struct FuseDr {
+    static constexpr int L = kWindow, V = 2, NT = 256, NW = NT / 64, ch = Store<TS>::ch;
+    static constexpr int CC = 8, win = L - 12, skip = 12;
+    static constexpr int d0_cols = CC + 5, t0_cols = CC + 4, t1_cols = 4, d1_cols = CC / 2 + 2;
+    static constexpr int pad = 16;  // floats before the first row
+    static constexpr int d0_off = pad, t0_off = d0_off + d0_cols * ch * L, t1_off = t0_off + t0_cols * 2 * L;
+    static constexpr int d1_off = t1_off + t1_cols * 3 * L;
+    static constexpr int lds = (d1_off + d1_cols * 2 * ch * L + kFusePad) * 4;
+};
+
+__device__ __forceinline__ float stored_t(float v, const float2 *) { return v; }
+__device__ __forceinline__ float stored_t(float v, const float4 *) { return v; }
+__device__ __forceinline__ float stored_t(float v, const half2_t *) { return (float)to_half(v); }
+__device__ __forceinline__ float stored_t(float v, const half4_t *) { return (float)to_half(v); }
+__device__ __forceinline__ float raw_t(float2 v) { return v.y; }
+__device__ __forceinline__ float raw_t(float4 v) { return v.w; }
+__device__ __forceinline__ float raw_t(half2_t v) { return (float)v.y; }
+__device__ __forceinline__ float raw_t(half4_t v) { return (float)v.w; }
+
+// One entry of dR_{m} (cone jj = 2 i + up, relative) of column c for V rows, from
+// LDS rows of the level below: own, the co-located probe's cone i; g, the odd
+// column's, at its shift; g2, the column before's, at twice that; t, t2 the
+// transmittances of Eq. 14 and of the doubled edge, as the level-by-level body
+// combines them.
+template <int V>
+__device__ __forceinline__ void fused_dr(const float (&own)[V], const float (&g)[V], const float (&t)[V],
+                                         bool in, const float (&g2)[V], const float (&t2)[V], bool in2,
+                                         float (&o)[V]) {
+#pragma unroll
+    for (int j = 0; j < V; ++j) {
+        o[j] = 0.5f * own[j];
+        o[j] = fmaf(in ? g[j] : 0.f, in ? t[j] : 0.f, o[j]);
+        o[j] = fmaf(0.5f * (in2 ? g2[j] : 0.f), in2 ? t2[j] : 0.f, o[j]);
+    }
+}
+
+template <typename TS>
+__device__ __forceinline__ void fuse_dr_block(const FuseArgs &a, char *lds, int tid) {
+    using F = FuseDr<TS>;
+    constexpr int V = F::V, L = F::L, NW = F::NW, CH = F::ch, CC = F::CC;
+    const int N = a.N, S = 1 << N, n = a.n;
+    const FuseTile t = fuse_tile(a);
+    const int x0 = t.x * CC, cols = S >> n, sb = 2 * t.ii - (1 << n);
+    const int own = F::skip + (a.win < S - t.y0 ? a.win : S - t.y0);
+    const size_t plane = (size_t)4 << (2 * N);
+    const unsigned q0 = (unsigned)t.q << (2 * N);
+    const int ii = t.ii;
+    const int wave = __builtin_amdgcn_readfirstlane(tid >> 6), lane = tid & 63;
+    float *l = reinterpret_cast<float *>(lds);
+    float *d0 = l + F::d0_off, *t0 = l + F::t0_off, *t1 = l + F::t1_off, *d1 = l + F::d1_off;
+    // window rows from 12 before the first stored one
+    const Rows<V> w(lane * V, t.y0 - F::skip, sb, S);
+    const TS *none = nullptr;
+    // dR_n and T_n's transmittances (directions ii, ii + 1), columns x0 - 6 on; all
+    // loads first
+    {
+        constexpr int DR = F::d0_cols * CH, DI = (DR + NW - 1) / NW;
+        constexpr int TR = F::t0_cols * 2, TI = (TR + NW - 1) / NW;
+        typename RawVec<8>::type dv[DI];
+        typename RawVec<sizeof(TS) * V == 32 ? 16 : sizeof(TS) * V>::type tv[TI][sizeof(TS) * V == 32 ? 2 : 1];
+        const float *D = a.R[0] + ((unsigned)t.q << (2 * N));
+        const TS *T = reinterpret_cast<const TS *>(a.T[0]) + (unsigned)t.q * a.te[0];
+#pragma unroll
+        for (int it = 0; it < DI; ++it) {
+            int i = it * NW + wave;
+            i = i < DR ? i : DR - 1;
+            const int p = i / CH, c = i % CH;
+            int x = x0 - 6 + p;
+            x = x < 0 ? 0 : x < cols ? x : cols - 1;
+            dv[it] = *reinterpret_cast<const typename RawVec<8>::type *>(
+                D + c * plane + (((unsigned)((x << n) | t.ii) << N) + (unsigned)w.y(p)));
+        }
+#pragma unroll
+        for (int it = 0; it < TI; ++it) {
+            int i = it * NW + wave;
+            i = i < TR ? i : TR - 1;
+            const int p = i >> 1, d = i & 1;
+            int x = x0 - 6 + p;
+            x = x < 0 ? 0 : x < cols ? x : cols - 1;
+            using R = std::remove_reference_t<decltype(tv[0][0])>;
+            const R *src = reinterpret_cast<const R *>(
+                T + (((unsigned)(x * ((1 << n) + 1) + t.ii + d) << N) + (unsigned)w.y(p)));
+            tv[it][0] = src[0];
+            if constexpr (sizeof(TS) * V == 32) tv[it][1] = src[1];
+        }
+#pragma unroll
+        for (int it = 0; it < DI; ++it) {
+            int i = it * NW + wave;
+            i = i < DR ? i : DR - 1;
+            *reinterpret_cast<typename RawVec<8>::type *>(d0 + i * L + w.r) = dv[it];
+        }
+#pragma unroll
+        for (int it = 0; it < TI; ++it) {
+            int i = it * NW + wave;
+            i = i < TR ? i : TR - 1;
+            TS e[V];
+            __builtin_memcpy(e, tv[it], sizeof(e));
+            *reinterpret_cast<float2 *>(t0 + i * L + w.r) = make_float2(raw_t(e[0]), raw_t(e[1]));
+        }
+    }
+    __syncthreads();
+    auto d0_row = [&](int p, int c) { return d0 + (p * CH + c) * L + w.r; };
+    auto t0_row = [&](int p, int d) { return t0 + (p * 2 + d) * L + w.r; };
+    auto t1_row = [&](int i, int d) { return t1 + (i * 3 + d) * L + w.r; };
+    auto d1_row = [&](int i, int u, int c) { return d1 + ((i * 2 + u) * CH + c) * L + w.r; };
+    // T_{n+1}'s transmittances at the columns x0/2 - 2 .. x0/2 + 1 (positions 2, 4,
+    // 6, 8 from x0 - 6), as the merge up builds them
+    for (int i = wave; i < F::t1_cols; i += NW) {
+        const int p = 2 + 2 * i, y = w.y(p) + sb;
+        float n0[V], n1[V], f00[V], f02[V], f10[V], f12[V];
+        ld_f<V>(t0_row(p, 0), n0);
+        ld_f<V>(t0_row(p, 1), n1);
+        ld_f<V>(t0_row(p + 1, 0), f00);
+        ld_f<V>(t0_row(p + 1, 0) + 2, f02);
+        ld_f<V>(t0_row(p + 1, 1), f10);
+        ld_f<V>(t0_row(p + 1, 1) + 2, f12);
+        const bool in0 = w.in(y), in1 = w.in(y + 2);
+        float e0[V], e1[V], e2[V];
+#pragma unroll
+        for (int j = 0; j < V; ++j) {
+            e0[j] = stored_t(n0[j] * (in0 ? f00[j] : 1.f), none);
+            e1[j] = stored_t(0.5f * (n1[j] * (in1 ? f02[j] : 1.f) + n0[j] * (in0 ? f10[j] : 1.f)), none);
+            e2[j] = stored_t(n1[j] * (in1 ? f12[j] : 1.f), none);
+        }
+        st_f<V>(t1_row(i, 0), e0);
+        st_f<V>(t1_row(i, 1), e1);
+        st_f<V>(t1_row(i, 2), e2);
+    }
+    // dR_{n+1} at the columns x0/2 - 2 .. x0/2 + CC/2 - 1
+    for (int i = wave; i < F::d1_cols * 2; i += NW) {
+        const int ci = i >> 1, up = i & 1, c = (x0 >> 1) - 2 + ci, p = 2 * ci + 2;  // column 2c
+        if (c < 0) continue;
+        const int y = w.y(p);
+        const int sh = 2 * up, yg = y - sb - sh, yg2 = y - 2 * (sb + sh);
+        const bool in = c >= 1 && w.in(yg), in2 = c > 1 && w.in(yg2);
+        float t[V], tn[V], t2[V];
+        ld_f<V>(t0_row(p - 1, up) - sh, t);
+        ld_f<V>(t0_row(p - 2, up) - 2 * sh, tn);
+#pragma unroll
+        for (int j = 0; j < V; ++j) t2[j] = stored_t(tn[j] * (w.in(yg) ? t[j] : 1.f), none);
+#pragma unroll
+        for (int c2 = 0; c2 < CH; ++c2) {
+            float f0[V], g[V], g2[V], o[V];
+            ld_f<V>(d0_row(p, c2), f0);
+            ld_f<V>(d0_row(p - 1, c2) - sh, g);
+            ld_f<V>(d0_row(p - 2, c2) - 2 * sh, g2);
+            fused_dr<V>(f0, g, t, in, g2, t2, in2, o);
+            st_f<V>(d1_row(ci, up, c2), o);
+            if (ci >= 2 && w.r >= F::skip && w.r < own)
+                st_f<V>(a.R[1] + c2 * plane + (q0 + ((unsigned)((c << (n + 1)) | (2 * ii + up)) << N) + (unsigned)y), o);
+        }
+    }
+    __syncthreads();
+    // dR_{n+2} at the columns x0/4 .. x0/4 + CC/4 - 1
+    for (int i = wave; i < CC; i += NW) {
+        const int Ci = i >> 2, k = i & 3, C = (x0 >> 2) + Ci, ci = 2 * Ci + 2;  // column 2C of level n+1
+        const int e = (k >> 1) + (k & 1), sh = 2 * e;
+        const int y = w.y(4 * Ci + 6), yg = y - 2 * sb - sh, yg2 = y - 2 * (2 * sb + sh);
+        const bool in = C >= 1 && w.in(yg), in2 = C > 1 && w.in(yg2);
+        float t[V], tn[V], t2[V];
+        ld_f<V>(t1_row(ci - 1, e) - sh, t);
+        ld_f<V>(t1_row(ci - 2, e) - 2 * sh, tn);
+#pragma unroll
+        for (int j = 0; j < V; ++j) t2[j] = stored_t(tn[j] * (w.in(yg) ? t[j] : 1.f), none);
+#pragma unroll
+        for (int c2 = 0; c2 < CH; ++c2) {
+            float f0[V], g[V], g2[V], o[V];
+            ld_f<V>(d1_row(ci, k >> 1, c2), f0);
+            ld_f<V>(d1_row(ci - 1, k >> 1, c2) - sh, g);
+            ld_f<V>(d1_row(ci - 2, k >> 1, c2) - 2 * sh, g2);
+            fused_dr<V>(f0, g, t, in, g2, t2, in2, o);
+            if (w.r >= F::skip && w.r < own)
+                st_f<V>(a.R[2] + c2 * plane + (q0 + ((unsigned)((C << (n + 2)) | (4 * ii + k)) << N) + (unsigned)y), o);
+        }
+    }
 }

@@ -148,6 +148,7 @@ struct BlurArgs {
 //         stored (the last always is), NULL where it stays on chip
 //   top   T[0] = T_n, levels = N - n: T[j] and R[j] as above (R[0] = R_n always)
 //   down  T[0] = T_n, R[2] = R_{n+2} read; R[0] = R_n, R[1] = R_{n+1} or NULL
+//   dr    T[0] = T_n, R[0] = dR_n read; R[1] = dR_{n+1}, R[2] = dR_{n+2}
 struct FuseArgs {
     void *T[5];
     float *R[4];
@@ -170,7 +171,7 @@ enum PhaseKind {
     PH_SEED_RGB, PH_UP_RGB, PH_DOWN_RGB, PH_TAIL_RGB,
     PH_DOWN_ADJ_RGB, PH_DT_RGB, PH_SEED_ADJ_RGB,
     // several levels of the merges in one kernel
-    PH_FUSE_UP, PH_FUSE_TOP, PH_FUSE_DOWN, PH_KIND_COUNT
+    PH_FUSE_UP, PH_FUSE_TOP, PH_FUSE_DOWN, PH_FUSE_DR, PH_KIND_COUNT
 };
 
 // One pass.  U = elements per thread of the elementwise phases (a tile covers

@@ -2735,6 +2735,12 @@ __global__ __launch_bounds__(FuseDown<TS>::NT) void hrc_fuse_down(Phase p) {
     fuse_down_block<TS>(p.a.fu, lds, (int)threadIdx.x);
 }
 
+template <typename TS>
+__global__ __launch_bounds__(FuseDr<TS>::NT) void hrc_fuse_dr(Phase p) {
+    __shared__ __align__(16) char lds[FuseDr<TS>::lds];
+    fuse_dr_block<TS>(p.a.fu, lds, (int)threadIdx.x);
+}
+
 // Kernel, block size and window of a fused phase.
 struct FusedKernel {
     void (*k)(Phase);
@@ -2766,6 +2772,8 @@ template <typename TS> FusedKernel fused_kernel_t(const Phase &p) {
             if (a.levels == 4) return top(i4);
     } else if (p.kind == PH_FUSE_DOWN) {
         return FusedKernel{hrc_fuse_down<TS>, FuseDown<TS>::NT, FuseDown<TS>::win};
+    } else if (p.kind == PH_FUSE_DR) {
+        return FusedKernel{hrc_fuse_dr<TS>, FuseDr<TS>::NT, FuseDr<TS>::win};
     }
     return FusedKernel{nullptr, 0, 0};
 }
@@ -2775,7 +2783,8 @@ static FusedKernel fused_kernel(const Phase &p) {
     return a.half ? fused_kernel_t<half2_t>(p) : fused_kernel_t<float2>(p);
 }
 static bool is_fused(const Phase &p) {
-    return p.kind == PH_FUSE_UP || p.kind == PH_FUSE_TOP || p.kind == PH_FUSE_DOWN;
+    return p.kind == PH_FUSE_UP || p.kind == PH_FUSE_TOP || p.kind == PH_FUSE_DOWN ||
+           p.kind == PH_FUSE_DR;
 }
 
 // ---------------------------------------------------------------------------
@@ -3013,6 +3022,8 @@ void size_fused(Phase &p) {
         a.lchunks = a.N - a.n - a.levels;
     else if (p.kind == PH_FUSE_DOWN)
         a.lchunks = a.N - a.n - (a.rgb && !a.half ? 2 : 3);  // FuseDown::CC columns
+    else if (p.kind == PH_FUSE_DR)
+        a.lchunks = a.N - a.n - 3;
     else
         a.lchunks = 0;
     for (int j = 0; j < 5; ++j)
@@ -3114,7 +3125,8 @@ hipError_t launch_phase(const Phase &p, hipStream_t s, hipEvent_t start, hipEven
         case PH_SEED_ADJ_RGB: k = hrc_seed_adj_rgb; break;
         case PH_FUSE_UP:
         case PH_FUSE_TOP:
-        case PH_FUSE_DOWN: {
+        case PH_FUSE_DOWN:
+        case PH_FUSE_DR: {
             const FusedKernel f = fused_kernel(p);
             if (!f.k) return hipErrorInvalidValue;
             k = f.k;
