@@ -82,7 +82,8 @@ typedef enum {
  * relative rounding of at most 2^-11 to what depends on it, so the fluence
  * stays within a relative N * 2^-11 of the FP32 result (about 5e-3 at
  * S = 1024) instead of 1e-4.  In hrc_backward the recomputed forward stores
- * its pyramid so while every adjoint stays FP32: every term of a gradient is a
+ * its pyramid so (T_2 and above: the levels below are folded on chip in FP32,
+ * in both directions) while every adjoint stays FP32: every term of a gradient is a
  * term of the fluence with one factor differentiated (all of one sign for
  * emission, and for sigma_t), so each gradient element stays within
  * N * 2^-11 times the same gradient taken with abs(grad_fluence).  L above

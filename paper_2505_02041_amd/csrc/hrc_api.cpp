@@ -167,7 +167,7 @@ static int tile_order(int N, int kind) {
 
 // The merges of one group of quadrants with several levels per kernel: T_2 up
 // to T_{n_top}, the top kernel from there to R_{n_top}, then down to R_2 two levels
-// at a time (a level left over, and R_1, are passes of their own).  The
+// at a time (a level left over is a pass of its own); the tail builds R_1 and R_0.  The
 // top kernel takes four levels (three with RGB intervals, twice as large in
 // LDS).  RGB in FP32 merges down level by level: its fused pair took 97 us at
 // 1024^2 against 2 x 33 us.  Only the levels at which a later kernel starts are stored, or all of
@@ -232,8 +232,7 @@ static int build_fused_merges(const Ws &w, const SolveBuffers &b, bool keep, boo
         size_fused(p);
         add(p);
     }
-    const int last = keep ? 1 : 2;
-    for (int n = n_top; n > last;) {
+    for (int n = n_top; n > kTracedLevels - 1;) {
         float *from = r_of(n);
         cur = 1 - cur;
         if (n - 2 >= kTracedLevels - 1 && !(rgb && !b.half)) {  // T_{n-1} is rebuilt from T_{n-2}: merged levels only
@@ -254,6 +253,13 @@ static int build_fused_merges(const Ws &w, const SolveBuffers &b, bool keep, boo
     }
     return cur;
 }
+
+// Image tile of the traced levels, the tail and its adjoint.  Up to 512^2 the
+// larger tile leaves CUs idle (256 blocks of it at 512^2): 16 takes 7.7, 13.2 and
+// 8.3 us there against 8.3, 18.3 and 10.1 (64^2: 5.1 and 9.1 against 5.8 and
+// 14.1); from 1024^2 on its relatively larger halo costs more: 16.2, 32.6 and 22.4
+// us against 12.0, 21.2 and 15.9 there.
+static int tail_tile(int N) { return N <= 9 ? 16 : 32; }
 
 // Two levels of the merge-down adjoint in one kernel: (T_n, dR_n) -> dR_{n+1},
 // dR_{n+2}.  It rebuilds T_{n+1} from T_n, so n >= 2 (the traced levels are no
@@ -298,10 +304,13 @@ int build_solve_phases(const Ws &w, const SolveBuffers &b, bool keep_all_r, cons
     for (int q0 = 0; recompute && q0 < kQuadrants; q0 += G) {
         p = Phase();
         p.kind = PH_SEED;
+        // level by level, the reverse reads T_0 and T_1 as well; its fused form
+        // folds them on chip (tail and tail adjoint)
+        const bool store_low = keep_all_r && !fused;
         p.a.seed = SeedArgs{b.eps,
                             b.sig,
-                            keep_all_r ? w.T(0) : nullptr,
-                            keep_all_r ? w.T(1) : nullptr,
+                            store_low ? w.T(0) : nullptr,
+                            store_low ? w.T(1) : nullptr,
                             w.T(2),
                             t_level_entries(N, 0),
                             t_level_entries(N, 1),
@@ -309,8 +318,8 @@ int build_solve_phases(const Ws &w, const SolveBuffers &b, bool keep_all_r, cons
                             N,
                             q0,
                             G,
-                            32,
-                            keep_all_r ? 0 : kTracedLevels - 1,
+                            tail_tile(N),
+                            store_low ? 0 : kTracedLevels - 1,
                             b.half};
         add(p);
         int cur = -1;
@@ -339,11 +348,14 @@ int build_solve_phases(const Ws &w, const SolveBuffers &b, bool keep_all_r, cons
             add(p);
             cur = o;
         }
-        if (b.F) {
+        // (for the reverse the fused solve's tail stores R_1, without F if none
+        // is asked for)
+        const bool tail_r1 = keep_all_r && fused;
+        if (b.F || tail_r1) {
             p = Phase();
             p.kind = PH_TAIL;
-            p.a.tail = TailArgs{b.eps, b.sig, keep_all_r ? w.R(2) : w.R(cur), gathered,
-                                N, q0, G, q0 > 0 ? 1 : 0, b.env, 32};
+            p.a.tail = TailArgs{b.eps, b.sig, keep_all_r ? w.R(2) : w.R(cur), b.F ? gathered : nullptr,
+                                N, q0, G, q0 > 0 ? 1 : 0, b.env, tail_tile(N), tail_r1 ? w.R(1) : nullptr};
             add(p);
         }
     }
@@ -365,10 +377,15 @@ int build_solve_phases(const Ws &w, const SolveBuffers &b, bool keep_all_r, cons
             dgathered = w.R(0);
         }
         p = Phase();
-        p.kind = PH_GATHER_ADJ;
-        p.a.ga = GatherAdjArgs{dgathered, w.dR(0), N};
+        if (fused) {
+            p.kind = PH_TAIL_ADJ;
+            p.a.ta = TailAdjArgs{dgathered, b.sig, w.dR(0), w.dR(1), w.dR(2), N, 0, tail_tile(N)};
+        } else {
+            p.kind = PH_GATHER_ADJ;
+            p.a.ga = GatherAdjArgs{dgathered, w.dR(0), N};
+        }
         add(p);
-        for (int n = 0; n + 1 < N; ++n) {
+        for (int n = fused ? 2 : 0; n + 1 < N; ++n) {
             if (fused && dr_pair(N, n)) {
                 add(fused_dr_phase(w, N, n++, b.half, false));
                 continue;
@@ -450,7 +467,7 @@ int build_rgb_forward_phases(const Ws &w, const SolveBuffers &b, Phase *out, int
 int build_rgb_backward_phases(const Ws &w, const SolveBuffers &b, Phase *out, int max_out,
                               bool recompute) {
     const int N = w.L.N;
-    const size_t SS = w.L.S * w.L.S, plane = kQuadrants * SS;
+    const size_t SS = w.L.S * w.L.S;
     int np = 0;
     auto add = [&](Phase p) {
         p.xblk = tile_order(N, p.kind);
@@ -462,16 +479,18 @@ int build_rgb_backward_phases(const Ws &w, const SolveBuffers &b, Phase *out, in
     float *gathered = b.blur ? w.dR(0) : b.F;
     if (recompute) {
         p.kind = PH_SEED_RGB;
-        p.a.seed = SeedArgs{b.eps, b.sig, w.T(0), w.T(1), w.T(2), t_level_entries(N, 0),
-                            t_level_entries(N, 1), t_level_entries(N, 2), N, 0, kQuadrants, 16, 0,
-                            b.half};
+        p.a.seed = SeedArgs{b.eps, b.sig, nullptr, nullptr, w.T(2), t_level_entries(N, 0),
+                            t_level_entries(N, 1), t_level_entries(N, 2), N, 0, kQuadrants, 16,
+                            kTracedLevels - 1, b.half};
         add(p);
         build_fused_merges(w, b, true, true, 0, kQuadrants, add);
+        // the tail stores R_1 for the reverse, and F if it is asked for
+        p = Phase();
+        p.kind = PH_TAIL_RGB;
+        p.a.tail = TailArgs{b.eps, b.sig, w.R(2), b.F ? gathered : nullptr, N, 0, kQuadrants, 0, nullptr,
+                            16, w.R(1)};
+        add(p);
         if (b.F) {
-            p = Phase();
-            p.kind = PH_TAIL_RGB;
-            p.a.tail = TailArgs{b.eps, b.sig, w.R(2), gathered, N, 0, kQuadrants, 0, nullptr, 16};
-            add(p);
             if (b.blur) {
                 for (int c = 0; c < 3; ++c) {
                     p = Phase();
@@ -494,13 +513,11 @@ int build_rgb_backward_phases(const Ws &w, const SolveBuffers &b, Phase *out, in
             }
             dgathered = w.R(0);
         }
-        for (int c = 0; c < 3; ++c) {
-            p = Phase();
-            p.kind = PH_GATHER_ADJ;
-            p.a.ga = GatherAdjArgs{dgathered + c * SS, w.dR(0) + c * plane, N};
-            add(p);
-        }
-        for (int n = 0; n + 1 < N; ++n) {
+        p = Phase();
+        p.kind = PH_TAIL_ADJ;
+        p.a.ta = TailAdjArgs{dgathered, b.sig, w.dR(0), w.dR(1), w.dR(2), N, 1, tail_tile(N)};
+        add(p);
+        for (int n = 2; n + 1 < N; ++n) {
             if (dr_pair(N, n)) {
                 add(fused_dr_phase(w, N, n++, b.half, true));
                 continue;
@@ -884,6 +901,16 @@ static int phase_passes(const Phase &p, int *kind, int *level) {
         case PH_FUSE_DOWN:
             add(PH_DOWN, p.a.fu.n + 1);
             add(PH_DOWN, p.a.fu.n);
+            break;
+        case PH_TAIL:
+            // without F it is the merge down of level 1 alone
+            if (p.a.tail.out) add(PH_TAIL, -1);
+            else add(PH_DOWN, 1);
+            break;
+        case PH_TAIL_ADJ:
+            add(PH_GATHER_ADJ, -1);
+            add(PH_DOWN_ADJ, 0);
+            add(PH_DOWN_ADJ, 1);
             break;
         case PH_FUSE_DR:
             add(PH_DOWN_ADJ, p.a.fu.n);

@@ -88,7 +88,13 @@ void phase_access(const Phase &p, std::vector<const void *> &rd, std::vector<con
             const TailArgs &a = p.a.tail;
             r(a.eps); r(a.sig); r(a.R2);
             if (a.accumulate) r(a.out);
-            w(a.out);
+            w(a.out); w(a.R1);
+            break;
+        }
+        case PH_TAIL_ADJ: {
+            const TailAdjArgs &a = p.a.ta;
+            r(a.dF); r(a.sig);
+            w(a.dR0); w(a.dR1); w(a.dR2);
             break;
         }
         case PH_GATHER_ADJ: r(p.a.ga.dF); w(p.a.ga.dR0); break;

@@ -100,6 +100,16 @@ struct TailArgs {
     int accumulate;          // add to out (the groups after the first) instead of storing
     const float *env;        // environment table (nullable)
     int tile;                // image tile side: 32 standalone, 16 in the persistent kernel
+    float *R1 = nullptr;     // R_1 as well, for the reverse (nullable; then out may be NULL)
+};
+// The adjoint of the gather and of the merge down of levels 0 and 1: dR_0, dR_1
+// and dR_2 of the four quadrants from dLoss/dF, the transmittances folded from
+// the attenuation.
+struct TailAdjArgs {
+    const float *dF, *sig;   // (RGB: three planes of dF)
+    float *dR0, *dR1, *dR2;  // (RGB: three planes of four quadrants each)
+    int N, rgb;
+    int tile;                // image tile side
 };
 struct GatherAdjArgs { const float *dF; float *dR0; int N; };
 struct DownAdjArgs {
@@ -171,7 +181,8 @@ enum PhaseKind {
     PH_SEED_RGB, PH_UP_RGB, PH_DOWN_RGB, PH_TAIL_RGB,
     PH_DOWN_ADJ_RGB, PH_DT_RGB, PH_SEED_ADJ_RGB,
     // several levels of the merges in one kernel
-    PH_FUSE_UP, PH_FUSE_TOP, PH_FUSE_DOWN, PH_FUSE_DR, PH_KIND_COUNT
+    PH_FUSE_UP, PH_FUSE_TOP, PH_FUSE_DOWN, PH_FUSE_DR,
+    PH_TAIL_ADJ, PH_KIND_COUNT
 };
 
 // One pass.  U = elements per thread of the elementwise phases (a tile covers
@@ -191,6 +202,7 @@ struct Phase {
         SeedAdjArgs sa;
         BlurArgs bl;
         FuseArgs fu;
+        TailAdjArgs ta;
         A() : dt{} {}
     } a;
 };

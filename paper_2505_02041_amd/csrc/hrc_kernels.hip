@@ -358,7 +358,7 @@ __device__ __forceinline__ void seed_level_rays(const I *iv, const SeedArgs &a, 
 // inside the persistent kernel, whose one LDS buffer serves every pass); the
 // per-ray arithmetic is the same for both.
 template <int TILE, typename TS>
-__device__ void body_seed(const SeedArgs &a, unsigned tile, char *lds, int tid) {
+__device__ __forceinline__ void body_seed(const SeedArgs &a, unsigned tile, char *lds, int tid) {
     using G = SeedTile<TILE>;
     float2 *iv = reinterpret_cast<float2 *>(lds);
     const int S = 1 << a.N;
@@ -825,7 +825,8 @@ __device__ void body_merge_down(const DownArgs &a, unsigned tile, int U, int tid
 // are folded here from the tile's pixel intervals, as the traced levels are
 // built, instead of being stored and read back: they hold only axis and
 // diagonal half pieces.  Quadrants are summed in order 0..3, and a later group
-// adds to the sum the earlier groups stored.
+// adds to the sum the earlier groups stored.  With KEEP the tile's own part of
+// R_1 is stored for the reverse (and F only if asked for).
 template <int TILE> struct TailTile {
     // T_2 rays run 4 pixels ahead of level-1 probes up to 2 columns past the
     // tile and +-4 rows around rows up to 2 beyond it
@@ -864,8 +865,8 @@ __device__ __forceinline__ float r2_at(const float *R2, int ro, int jj, int y, i
     return in ? v : fill;
 }
 
-template <int TILE>
-__device__ void body_tail(const TailArgs &a, unsigned tile, char *lds, int tid) {
+template <int TILE, bool KEEP>
+__device__ __forceinline__ void body_tail(const TailArgs &a, unsigned tile, char *lds, int tid) {
     using G = TailTile<TILE>;
     constexpr int H = G::halo, P = G::pitch, RR = G::r1rows, AP = G::acc_pitch;
     constexpr int span2 = G::span * G::span;
@@ -898,6 +899,7 @@ __device__ void body_tail(const TailArgs &a, unsigned tile, char *lds, int tid) 
     for (int g = 0; g < a.nq; ++g) {
         const int q = a.q0 + g;
         const float *R2 = a.R2 + (size_t)g * S * S;
+        float *R1 = KEEP ? a.R1 + (size_t)g * S * S : nullptr;
         const float *envq = a.env ? a.env + (size_t)q * kConeTable : nullptr;
         // angular fluences beyond the grid (uniform over the tile)
         const float e10 = env_fluence(envq, 1, 0), e11 = env_fluence(envq, 1, 1);
@@ -940,6 +942,13 @@ __device__ void body_tail(const TailArgs &a, unsigned tile, char *lds, int tid) 
             }
             r1[(2 * j) * RR + wl] = v0;
             r1[(2 * j + 1) * RR + wl] = v1;
+            // the tile's own part of R_1, for the reverse (its last column is
+            // the next tile's first)
+            if (KEEP && j < TILE / 2 && cp > 0 && cp < (S >> 1) && (unsigned)(wl - 2) < (unsigned)TILE &&
+                (unsigned)w < (unsigned)S) {
+                R1[(unsigned)((2 * cp) << N) + (unsigned)w] = v0;
+                R1[(unsigned)((2 * cp + 1) << N) + (unsigned)w] = v1;
+            }
         }
         // R_1 at even level-1 columns (Eq. 15-17 at level 1, through the even directions of T_2)
         constexpr int n_even = (TILE / 4) * RR;
@@ -971,8 +980,14 @@ __device__ void body_tail(const TailArgs &a, unsigned tile, char *lds, int tid) 
             }
             r1[(2 * j) * RR + wl] = v0;
             r1[(2 * j + 1) * RR + wl] = v1;
+            if (KEEP && cp > 0 && cp < (S >> 1) && (unsigned)(wl - 2) < (unsigned)TILE &&
+                (unsigned)w < (unsigned)S) {
+                R1[(unsigned)((2 * cp) << N) + (unsigned)w] = v0;
+                R1[(unsigned)((2 * cp + 1) << N) + (unsigned)w] = v1;
+            }
         }
         __syncthreads();
+        if (KEEP && !a.out) continue;  // R_1 alone
         // R_0 at x = u + 1 for every pixel (u, w) of the tile, added to the sum.
         // A thread keeps its row w; its column offsets ul are all even (x
         // odd) in the first half of the passes and all odd in the second, so
@@ -1019,6 +1034,7 @@ __device__ void body_tail(const TailArgs &a, unsigned tile, char *lds, int tid) 
         }
     }
     __syncthreads();
+    if (KEEP && !a.out) return;
 #pragma unroll
     for (int it = 0; it < TILE * TILE / 256; ++it) {
         const int i = tid + 256 * it;
@@ -1082,6 +1098,170 @@ __device__ void body_gather_adj(const GatherAdjArgs &a, unsigned tile, char *lds
         }
     }
     __syncthreads();
+}
+
+// Adjoint of the gather and of the merge down of levels 0 and 1, per image tile
+// and every quadrant: dR_0 (dF one column on), dR_1 and dR_2 in gather form (as
+// body_merge_down_adj), their transmittances T_0, T_1 and the even directions of
+// T_2 folded from the tile's pixels as the traced levels fold them (products of
+// axis and diagonal half pieces).  dR_1 lies in LDS over the columns and rows
+// dR_2 reads.  A quadrant looks back at most seven columns and seven rows, and
+// its rays end one column ahead, so the tile needs a 7-pixel halo.  dF is 0
+// outside the grid, and so is dR_1, so no lookup needs a test; the quadrant is a
+// template parameter, so every LDS offset is an immediate.  At 1024^2 22 us (35
+// with run-time offsets and tests), for 46 in the three passes it stands for.
+template <int TILE, int CH> struct TailAdjTile {
+    static constexpr int halo = 7, span = TILE + 2 * halo, pitch = span + 1, plane = span * pitch;
+    static constexpr int cols = TILE / 2 + 2, rows = TILE + 8;  // dR_1: from 2 columns and 4 rows before
+    static constexpr int d1_plane = cols * 2 * rows;
+    static constexpr int lds = ((2 + CH) * plane + CH * d1_plane) * 4;
+    // LDS offset of a frame displacement of (du, dw) pixels in quadrant Q
+    static constexpr int off(int Q, int du, int dw) {
+        return Q == 0 ? dw * pitch + du : Q == 1 ? dw * pitch - du : Q == 2 ? du * pitch + dw : -du * pitch + dw;
+    }
+};
+
+// Transmittance of traced ray `sid` whose probe lies (du, dw) from tp's pixel
+// (pieces in order from the probe, as tail_ray).
+template <typename G, int Q, int sid, int pieces, int du, int dw>
+__device__ __forceinline__ float tail_trans(const float *tp) {
+    float t = tp[kHpLen[sid][0] * G::plane + G::off(Q, du, dw)];
+#pragma unroll
+    for (int j = 1; j < pieces; ++j)
+        t = t * tp[kHpLen[sid][j] * G::plane + G::off(Q, du + kHpDu[sid][j], dw + kHpDw[sid][j])];
+    return t;
+}
+
+// One quadrant of a tile: tt the two transmittance planes, df the dF planes, d1
+// the LDS of dR_1.
+template <int TILE, int CH, int Q>
+__device__ __forceinline__ void tail_adj_quadrant(const TailAdjArgs &a, int r0, int c0, const float *tt,
+                                                  const float *df, float *d1, int tid) {
+    using G = TailAdjTile<TILE, CH>;
+    constexpr int H = G::halo, P = G::pitch, PL = G::plane, RR = G::rows;
+    const int N = a.N, S = 1 << N;
+    const unsigned SS = 1u << (2 * N);
+    const size_t plane4 = (size_t)4 * SS;
+    // the frame of the quadrant, as in the tail
+    const int u_lo = Q == 0 ? c0 : Q == 1 ? S - TILE - c0 : Q == 2 ? r0 : S - TILE - r0;
+    const int w_lo = Q < 2 ? r0 : c0;
+    constexpr int base = Q == 1 ? H * P + TILE - 1 + H : Q == 3 ? (TILE - 1 + H) * P + H : H * P + H;
+    constexpr int su = Q == 0 ? 1 : Q == 1 ? -1 : Q == 2 ? P : -P, sw = Q < 2 ? P : 1;
+    // dR_0(x, y) = dF at frame pixel (x - 1, y), 0 at x = 0
+#pragma unroll
+    for (int it = 0; it < TILE * TILE / 256; ++it) {
+        const int i = tid + 256 * it, xl = i / TILE, yl = i % TILE, x = u_lo + xl, y = w_lo + yl;
+        if (x >= 0 && x < S && y < S) {
+            const float *p = df + base + (xl - 1) * su + yl * sw;
+#pragma unroll
+            for (int ch = 0; ch < CH; ++ch)
+                a.dR0[ch * plane4 + (Q * SS + ((unsigned)x << N) + (unsigned)y)] = p[ch * PL];
+        }
+    }
+    // dR_1 at columns u_lo/2 - 2 .. u_lo/2 + TILE/2 - 1, both cones, from four rows
+    // before the tile to four after
+    constexpr int n1 = G::cols * RR;
+    for (int i = tid; i < n1; i += 256) {
+        const int yl = i % RR, ci = i / RR, c = u_lo / 2 - 2 + ci, y = w_lo - 4 + yl;
+        // pixel (2c, y); dR_0(2c) is the pixel before it
+        const int px = base + (2 * ci - 4) * su + (yl - 4) * sw;
+        const bool in = (unsigned)c < (unsigned)(S >> 1) && (unsigned)y < (unsigned)S;
+        const float *tp = tt + px;
+        // Eq. 14: T_0(2c-1, k) one row up or down; Eq. 17: T_1(c-1, 2k) two rows
+        const float ta = tail_trans<G, Q, 0, 2, -1, 1>(tp), tb = tail_trans<G, Q, 1, 2, -1, -1>(tp);
+        const float t2a = tail_trans<G, Q, 2, 4, -2, 2>(tp), t2b = tail_trans<G, Q, 4, 4, -2, -2>(tp);
+#pragma unroll
+        for (int ch = 0; ch < CH; ++ch) {
+            const float *dp = df + ch * PL + px;
+            const float own = 0.5f * dp[G::off(Q, -1, 0)];
+            float va = fmaf(dp[G::off(Q, -2, 1)], ta, own), vb = fmaf(dp[G::off(Q, -2, -1)], tb, own);
+            va = fmaf(0.5f * dp[G::off(Q, -3, 2)], t2a, va);
+            vb = fmaf(0.5f * dp[G::off(Q, -3, -2)], t2b, vb);
+            va = in ? va : 0.f;
+            vb = in ? vb : 0.f;
+            d1[ch * G::d1_plane + 2 * ci * RR + yl] = va;
+            d1[ch * G::d1_plane + (2 * ci + 1) * RR + yl] = vb;
+            if (in && ci >= 2 && (unsigned)(yl - 4) < (unsigned)TILE) {
+                float *o = a.dR1 + ch * plane4 + (Q * SS + ((unsigned)(2 * c) << N) + (unsigned)y);
+                o[0] = va;
+                o[S] = vb;
+            }
+        }
+    }
+    __syncthreads();
+    // dR_2 at the tile's columns, the four cones together: T_1(2C-1, e) and T_2(C-1,
+    // 2e), e = 0, 1, 2
+#pragma unroll
+    for (int it = 0; it < (TILE / 4 * TILE + 255) / 256; ++it) {
+        const int i = tid + 256 * it, yl = i % TILE, Ci = i / TILE, C = u_lo / 4 + Ci, y = w_lo + yl;
+        if (i >= TILE / 4 * TILE || C < 0 || C >= (S >> 2) || y >= S) continue;
+        const float *tp = tt + base + 4 * Ci * su + yl * sw;  // pixel (4C, y)
+        const float t[3] = {tail_trans<G, Q, 2, 4, -2, 2>(tp), tail_trans<G, Q, 3, 4, -2, 0>(tp),
+                            tail_trans<G, Q, 4, 4, -2, -2>(tp)};
+        const float t2[3] = {tail_trans<G, Q, 5, 8, -4, 4>(tp), tail_trans<G, Q, 7, 8, -4, 0>(tp),
+                             tail_trans<G, Q, 9, 8, -4, -4>(tp)};
+#pragma unroll
+        for (int ch = 0; ch < CH; ++ch)
+#pragma unroll
+            for (int jj = 0; jj < 4; ++jj) {
+                const int ii = jj >> 1, e = ii + (jj & 1), dy = 2 - 2 * e;
+                // column 2C is number 2 Ci + 2 of the LDS columns
+                const float *dc = d1 + ch * G::d1_plane + (4 * Ci + 4 + ii) * RR + yl + 4;
+                float v = 0.5f * dc[0];
+                v = fmaf(dc[-2 * RR + dy], t[e], v);
+                v = fmaf(0.5f * dc[-4 * RR + 2 * dy], t2[e], v);
+                a.dR2[ch * plane4 + (Q * SS + ((unsigned)((C << 2) | jj) << N) + (unsigned)y)] = v;
+            }
+    }
+    __syncthreads();  // dR_1's LDS is the next quadrant's
+}
+
+template <int TILE, int CH>
+__device__ __forceinline__ void body_tail_adj(const TailAdjArgs &a, unsigned tile, char *lds, int tid) {
+    using G = TailAdjTile<TILE, CH>;
+    constexpr int H = G::halo, P = G::pitch, PL = G::plane;
+    float *tt = reinterpret_cast<float *>(lds);  // axis, diagonal half pieces; then dF
+    float *df = tt + 2 * PL, *d1 = df + CH * PL;
+    const int N = a.N, S = 1 << N;
+    const size_t SS = (size_t)S * S;
+    const int tiles = (S + TILE - 1) / TILE;
+    const int r0 = (int)(tile / tiles) * TILE, c0 = (int)(tile % tiles) * TILE;
+    constexpr int cells = G::span * G::span, NI = (cells + 255) / 256;
+    float gv[NI], fv[CH][NI];
+    bool inside[NI];
+#pragma unroll
+    for (int it = 0; it < NI; ++it) {
+        const int i = tid + 256 * it;
+        const int r = r0 - H + i / G::span, c = c0 - H + i % G::span;
+        inside[it] = i < cells && (unsigned)r < (unsigned)S && (unsigned)c < (unsigned)S;
+        const unsigned o = inside[it] ? (unsigned)(r * S + c) : 0u;
+        gv[it] = a.sig[o];
+#pragma unroll
+        for (int ch = 0; ch < CH; ++ch) fv[ch][it] = a.dF[ch * SS + o];
+    }
+#pragma unroll
+    for (int it = 0; it < NI; ++it) {
+        pin(gv[it]);
+#pragma unroll
+        for (int ch = 0; ch < CH; ++ch) pin(fv[ch][it]);
+    }
+#pragma unroll
+    for (int it = 0; it < NI; ++it) {
+        const int i = tid + 256 * it;
+        if (i < cells) {
+            const float g = inside[it] ? gv[it] : 0.f;
+            const int l = (i / G::span) * P + i % G::span;
+            tt[l] = exp_neg(g * 0.5f);
+            tt[PL + l] = exp_neg(g * kH2);
+#pragma unroll
+            for (int ch = 0; ch < CH; ++ch) df[ch * PL + l] = inside[it] ? fv[ch][it] : 0.f;
+        }
+    }
+    __syncthreads();
+    tail_adj_quadrant<TILE, CH, 0>(a, r0, c0, tt, df, d1, tid);
+    tail_adj_quadrant<TILE, CH, 1>(a, r0, c0, tt, df, d1, tid);
+    tail_adj_quadrant<TILE, CH, 2>(a, r0, c0, tt, df, d1, tid);
+    tail_adj_quadrant<TILE, CH, 3>(a, r0, c0, tt, df, d1, tid);
 }
 
 // R at (row, y) and (row, y+1), the row starting at element `row` of `base`
@@ -1351,7 +1531,9 @@ __device__ void body_dT_t(const DTArgs &a, unsigned tile, int U, int tid) {
         const unsigned rc = row - (unsigned)q * rpq;
         const int c = (int)div_rows(rc, (unsigned)dirs), k = (int)(rc - (unsigned)c * dirs);
         if (pairs) {
-            dT_output<TS, ENV>(a, q, 2 * c, k, y);
+            // T_0 is read at odd columns only: its adjoint is 0 at the even
+            // ones, which are neither stored nor read
+            if (n > 0) dT_output<TS, ENV>(a, q, 2 * c, k, y);
             dT_output<TS, ENV>(a, q, 2 * c + 1, k, y);
         } else {
             dT_output<TS, ENV>(a, q, c, k, y);
@@ -1485,9 +1667,11 @@ __device__ __forceinline__ void seed_adj_dir(__amdgpu_buffer_rsrc_t dTq, int S, 
     constexpr int dirs = (1 << n) + 1, pieces = 2 << n;
     constexpr int L = piece_len(n, k);
     constexpr int plane = kAdjSpan * kAdjPitch;
+    // level 0 has adjoints at odd probe columns only: one of the two pieces
+    constexpr int w0 = n == 0 && (rho & 1) == 0 ? 1 : 0, w1 = n == 0 && (rho & 1) ? 1 : 2;
     float2 g[2];
 #pragma unroll
-    for (int which = 0; which < 2; ++which) {
+    for (int which = w0; which < w1; ++which) {
         const int j = adj_piece(n, rho, which);
         // the probe's column (u - du_j) / 2^n is exact: u = rho (mod 2^n)
         const int cj = (piece_du(j) - (rho & ((1 << n) - 1))) >> n;
@@ -1501,7 +1685,7 @@ __device__ __forceinline__ void seed_adj_dir(__amdgpu_buffer_rsrc_t dTq, int S, 
         g[which] = make_float2(__uint_as_float(v[0]), __uint_as_float(v[1]));
     }
 #pragma unroll
-    for (int which = 0; which < 2; ++which) {
+    for (int which = w0; which < w1; ++which) {
         const int j = adj_piece(n, rho, which);
         float pre = 1.f;
         float2 suf = make_float2(0.f, 1.f);
@@ -1541,7 +1725,7 @@ template <int Q, int rho>
 __device__ __forceinline__ void seed_adj_levels(const SeedAdjArgs &a, int u, int w,
                                                 const float2 *ivp, AdjSums &sum) {
     const int S = 1 << a.N;
-    seed_adj_level<Q, 0, 0>(dT_resource(a.dT0 + (size_t)Q * a.e0, a.e0), S, u, w, ivp, sum);
+    seed_adj_level<Q, 0, rho & 1>(dT_resource(a.dT0 + (size_t)Q * a.e0, a.e0), S, u, w, ivp, sum);
     seed_adj_level<Q, 1, rho & 1>(dT_resource(a.dT1 + (size_t)Q * a.e1, a.e1), S, u, w, ivp, sum);
     seed_adj_level<Q, 2, rho>(dT_resource(a.dT2 + (size_t)Q * a.e2, a.e2), S, u, w, ivp, sum);
 }
@@ -2072,10 +2256,17 @@ __device__ void body_tail_rgb(const TailArgs &a, unsigned tile, char *lds, int t
                              fmaf(t2.w, r2_at3(R2c, ro, 3, w + 2, S, cin), c_cone[6] * chan(t2, ch));
                 }
             }
+            const bool keep = a.R1 && j < TILE / 2 && cp > 0 && cp < (S >> 1) &&
+                              (unsigned)(wl - 2) < (unsigned)TILE && (unsigned)w < (unsigned)S;
 #pragma unroll
             for (int ch = 0; ch < 3; ++ch) {
                 r1[ch * R1P + (2 * j) * RR + wl] = v0[ch];
                 r1[ch * R1P + (2 * j + 1) * RR + wl] = v1[ch];
+                if (keep) {  // the tile's own part of R_1, for the reverse
+                    float *R1 = a.R1 + ch * R2plane + (size_t)g * SS;
+                    R1[((size_t)(2 * cp) << N) + w] = v0[ch];
+                    R1[((size_t)(2 * cp + 1) << N) + w] = v1[ch];
+                }
             }
         }
         // R_1 at even level-1 columns (Eq. 15-17 at level 1)
@@ -2105,13 +2296,21 @@ __device__ void body_tail_rgb(const TailArgs &a, unsigned tile, char *lds, int t
                                      fmaf(t4.w, r2_at3(R2c, ro1, 3, w + 4, S, cin), c_cone[6] * chan(t4, ch)));
                 }
             }
+            const bool keep = a.R1 && j < TILE / 2 && cp > 0 && cp < (S >> 1) &&
+                              (unsigned)(wl - 2) < (unsigned)TILE && (unsigned)w < (unsigned)S;
 #pragma unroll
             for (int ch = 0; ch < 3; ++ch) {
                 r1[ch * R1P + (2 * j) * RR + wl] = v0[ch];
                 r1[ch * R1P + (2 * j + 1) * RR + wl] = v1[ch];
+                if (keep) {  // the tile's own part of R_1, for the reverse
+                    float *R1 = a.R1 + ch * R2plane + (size_t)g * SS;
+                    R1[((size_t)(2 * cp) << N) + w] = v0[ch];
+                    R1[((size_t)(2 * cp + 1) << N) + w] = v1[ch];
+                }
             }
         }
         __syncthreads();
+        if (!a.out) continue;  // R_1 alone
         // R_0 at x = u + 1 for every pixel (u, w) of the tile, added to the sums
         constexpr int SP = 256 / TILE, IT = TILE * TILE / 256;
         const int wl = tid % TILE, w = w_lo + wl, slot0 = tid / TILE;
@@ -2155,6 +2354,7 @@ __device__ void body_tail_rgb(const TailArgs &a, unsigned tile, char *lds, int t
         }
     }
     __syncthreads();
+    if (!a.out) return;
     for (int i = tid; i < TILE * TILE; i += 256) {
         const int rl = i / TILE, cl = i % TILE;
         const int r = r0 + rl, c = c0 + cl;
@@ -2279,6 +2479,7 @@ __device__ void body_dT_rgb(const DTArgs &a, unsigned tile, int U, int tid) {
         const int q = (row >= rpq) + (row >= 2 * rpq) + (row >= 3 * rpq);
         const unsigned r = row - (unsigned)q * rpq;
         const int x = (int)div_rows(r, (unsigned)dirs), k = (int)(r - (unsigned)x * dirs);
+        if (n == 0 && (x & 1) == 0) continue;  // 0, not read: as body_dT_t
         // (a) merge down at level n, odd x (Eq. 14)
         float2 ag[2][3], ar[2][3];
         float aA[2] = {0.f, 0.f};
@@ -2452,9 +2653,11 @@ __device__ __forceinline__ void seed_adj_dir_rgb(__amdgpu_buffer_rsrc_t dTq, int
     constexpr int dirs = (1 << n) + 1, pieces = 2 << n;
     constexpr int L = piece_len(n, k);
     constexpr int plane = kAdjSpan * kAdjPitch;
+    // as seed_adj_dir: level 0 at odd probe columns only
+    constexpr int w0 = n == 0 && (rho & 1) == 0 ? 1 : 0, w1 = n == 0 && (rho & 1) ? 1 : 2;
     float4 g[2];
 #pragma unroll
-    for (int which = 0; which < 2; ++which) {
+    for (int which = w0; which < w1; ++which) {
         const int j = adj_piece(n, rho, which);
         const int cj = (piece_du(j) - (rho & ((1 << n) - 1))) >> n;
         const int dwj = piece_dw(n, k, j);
@@ -2467,7 +2670,7 @@ __device__ __forceinline__ void seed_adj_dir_rgb(__amdgpu_buffer_rsrc_t dTq, int
                                __uint_as_float(v[3]));
     }
 #pragma unroll
-    for (int which = 0; which < 2; ++which) {
+    for (int which = w0; which < w1; ++which) {
         const int j = adj_piece(n, rho, which);
         float pre = 1.f;
         float4 suf = empty_interval<float4>();
@@ -2505,7 +2708,7 @@ __device__ __forceinline__ void seed_adj_levels_rgb(const SeedAdjArgs &a, int u,
                                                     const float4 *ivp, AdjSumsRgb &sum) {
     const int S = 1 << a.N;
     // RGB levels hold 16-byte entries: quadrant Q starts Q e_n entries in
-    seed_adj_level_rgb<Q, 0, 0>(dT_resource_rgb(a.dT0 + (size_t)Q * a.e0 * 2, a.e0), S, u, w, ivp, sum);
+    seed_adj_level_rgb<Q, 0, rho & 1>(dT_resource_rgb(a.dT0 + (size_t)Q * a.e0 * 2, a.e0), S, u, w, ivp, sum);
     seed_adj_level_rgb<Q, 1, rho & 1>(dT_resource_rgb(a.dT1 + (size_t)Q * a.e1 * 2, a.e1), S, u, w, ivp, sum);
     seed_adj_level_rgb<Q, 2, rho>(dT_resource_rgb(a.dT2 + (size_t)Q * a.e2 * 2, a.e2), S, u, w, ivp, sum);
 }
@@ -2622,7 +2825,7 @@ __device__ __forceinline__ void run_phase(const Phase &p, unsigned tile, char *l
         case PH_SEED: body_seed<16, float2>(p.a.seed, tile, lds, tid); break;  // planner sets tile 16
         case PH_UP: body_merge_up<float2>(p.a.up, tile, p.U, tid); break;
         case PH_DOWN: body_merge_down<float2>(p.a.down, tile, p.U, tid); break;
-        case PH_TAIL: body_tail<16>(p.a.tail, tile, lds, tid); break;  // planner sets tile 16
+        case PH_TAIL: body_tail<16, false>(p.a.tail, tile, lds, tid); break;  // planner sets tile 16
         case PH_GATHER_ADJ: body_gather_adj(p.a.ga, tile, lds, tid); break;
         case PH_DOWN_ADJ: body_merge_down_adj<float2>(p.a.da, tile, p.U, tid); break;
         case PH_DT: body_dT<float2>(p.a.dt, tile, p.U, tid); break;
@@ -2656,6 +2859,10 @@ __global__ __launch_bounds__(256) void hrc_seed(Phase p) {
     __shared__ __align__(16) char lds[SeedTile<32>::lds];
     body_seed<32, float2>(p.a.seed, xcd_tile(blockIdx.x, gridDim.x), lds, ltid());
 }
+template <typename TS> __global__ __launch_bounds__(256) void hrc_seed_16(Phase p) {
+    __shared__ __align__(16) char lds[SeedTile<16>::lds];
+    body_seed<16, TS>(p.a.seed, xcd_tile(blockIdx.x, gridDim.x), lds, ltid());
+}
 __global__ __launch_bounds__(256) void hrc_seed_f16(Phase p) {
     __shared__ __align__(16) char lds[SeedTile<32>::lds];
     body_seed<32, half2_t>(p.a.seed, xcd_tile(blockIdx.x, gridDim.x), lds, ltid());
@@ -2670,9 +2877,9 @@ __global__ __launch_bounds__(256) void hrc_blur(Phase p) {
 __global__ __launch_bounds__(256) void hrc_blur_adj(Phase p) {
     body_blur_adj(p.a.bl, xcd_tile(blockIdx.x, gridDim.x), ltid());
 }
-__global__ __launch_bounds__(256) void hrc_tail(Phase p) {
-    __shared__ __align__(16) char lds[TailTile<32>::lds];
-    body_tail<32>(p.a.tail, xcd_tile(blockIdx.x, gridDim.x), lds, ltid());
+template <int TILE, bool KEEP> __global__ __launch_bounds__(256) void hrc_tail(Phase p) {
+    __shared__ __align__(16) char lds[TailTile<TILE>::lds];
+    body_tail<TILE, KEEP>(p.a.tail, xcd_tile(blockIdx.x, gridDim.x), lds, ltid());
 }
 __global__ __launch_bounds__(256) void hrc_seed_rgb(Phase p) {
     __shared__ __align__(16) char lds[SeedTileRgb<16>::lds];
@@ -2713,6 +2920,10 @@ __global__ __launch_bounds__(256) void hrc_interval_adj_rgb_f16(Phase p) {
 __global__ __launch_bounds__(256) void hrc_seed_adj_rgb(Phase p) {
     __shared__ __align__(16) char lds[kSeedAdjRgbLds];
     body_seed_adj_rgb(p.a.sa, xcd_tile(blockIdx.x, gridDim.x), lds, ltid());
+}
+template <int TILE, int CH> __global__ __launch_bounds__(256) void hrc_tail_adj(Phase p) {
+    __shared__ __align__(16) char lds[TailAdjTile<TILE, CH>::lds];
+    body_tail_adj<TILE, CH>(p.a.ta, xcd_tile(blockIdx.x, gridDim.x), lds, ltid());
 }
 __global__ __launch_bounds__(256) void hrc_gather_adj(Phase p) {
     __shared__ __align__(16) char lds[kGatherAdjLds];
@@ -3057,6 +3268,7 @@ unsigned phase_tiles(const Phase &p) {
             case PH_DOWN_ADJ_RGB: return p.a.da.N;
             case PH_DT_RGB: return p.a.dt.N;
             case PH_SEED_ADJ_RGB: return p.a.sa.N;
+            case PH_TAIL_ADJ: return p.a.ta.N;
         }
         return 0;
     }();
@@ -3066,6 +3278,10 @@ unsigned phase_tiles(const Phase &p) {
     switch (p.kind) {
         case PH_TAIL: {
             const unsigned t = (unsigned)((S + p.a.tail.tile - 1) / p.a.tail.tile);
+            return t * t;
+        }
+        case PH_TAIL_ADJ: {
+            const unsigned t = (unsigned)((S + p.a.ta.tile - 1) / p.a.ta.tile);
             return t * t;
         }
         case PH_GATHER_ADJ: return 4 * t32 * t32;
@@ -3106,11 +3322,21 @@ hipError_t launch_phase(const Phase &p, hipStream_t s, hipEvent_t start, hipEven
     void (*k)(Phase) = nullptr;
     unsigned threads = 256;
     switch (p.kind) {
-        case PH_SEED: k = p.a.seed.half ? hrc_seed_f16 : hrc_seed; break;
+        case PH_SEED:
+            if (p.a.seed.tile == 16) k = p.a.seed.half ? hrc_seed_16<half2_t> : hrc_seed_16<float2>;
+            else k = p.a.seed.half ? hrc_seed_f16 : hrc_seed;
+            break;
         case PH_UP: k = p.a.up.half ? hrc_merge_up_f16 : hrc_merge_up; break;
         case PH_DOWN: k = p.a.down.half ? hrc_merge_down_f16 : hrc_merge_down; break;
-        case PH_TAIL: k = hrc_tail; break;
+        case PH_TAIL:
+            if (p.a.tail.tile == 16) k = p.a.tail.R1 ? hrc_tail<16, true> : hrc_tail<16, false>;
+            else k = p.a.tail.R1 ? hrc_tail<32, true> : hrc_tail<32, false>;
+            break;
         case PH_GATHER_ADJ: k = hrc_gather_adj; break;
+        case PH_TAIL_ADJ:
+            if (p.a.ta.tile == 16) k = p.a.ta.rgb ? hrc_tail_adj<16, 3> : hrc_tail_adj<16, 1>;
+            else k = p.a.ta.rgb ? hrc_tail_adj<32, 3> : hrc_tail_adj<32, 1>;
+            break;
         case PH_DOWN_ADJ: k = p.a.da.half ? hrc_merge_down_adj_f16 : hrc_merge_down_adj; break;
         case PH_DT: k = p.a.dt.half ? hrc_interval_adj_f16 : hrc_interval_adj; break;
         case PH_SEED_ADJ: k = hrc_seed_adj; break;
