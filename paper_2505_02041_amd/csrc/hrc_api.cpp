@@ -169,8 +169,7 @@ static int tile_order(int N, int kind) {
 // to T_{n_top}, the top kernel from there to R_{n_top}, then down to R_2 two levels
 // at a time (a level left over is a pass of its own); the tail builds R_1 and R_0.  The
 // top kernel takes four levels (three with RGB intervals, twice as large in
-// LDS).  RGB in FP32 merges down level by level: its fused pair took 97 us at
-// 1024^2 against 2 x 33 us.  Only the levels at which a later kernel starts are stored, or all of
+// LDS).  Only the levels at which a later kernel starts are stored, or all of
 // them when they are kept for the reverse.  Returns the buffer index of the
 // last R level (not keeping).
 template <typename Add>
@@ -195,6 +194,11 @@ static int build_fused_merges(const Ws &w, const SolveBuffers &b, bool keep, boo
         return p;
     };
     Phase p;
+    // RGB in FP32 merges down two levels at a time where that saves storing the
+    // levels between and the grid is past the caches: at 1024^2 81 and 86 us a
+    // pair against 73 and 82, but the merges up before it 82 against 107; at 512^2
+    // (two levels 25 against 17) it would not
+    const bool pair_down = !rgb || b.half || (!keep && N >= 10);
     const int max_up = rgb ? 3 : 4;
     for (int n = kTracedLevels - 1; n < n_top;) {
         int g = std::min(n_top - n, max_up);
@@ -207,7 +211,7 @@ static int build_fused_merges(const Ws &w, const SolveBuffers &b, bool keep, boo
         } else {
             p = fused(PH_FUSE_UP, n, g);
             for (int j = 1; j <= g; ++j)
-                if (keep || j == g || (rgb && !b.half) || (n_top - n - j) % 2 == 0)
+                if (keep || j == g || !pair_down || (n_top - n - j) % 2 == 0)
                     p.a.fu.T[j] = w.T(n + j);
             size_fused(p);
         }
@@ -235,7 +239,7 @@ static int build_fused_merges(const Ws &w, const SolveBuffers &b, bool keep, boo
     for (int n = n_top; n > kTracedLevels - 1;) {
         float *from = r_of(n);
         cur = 1 - cur;
-        if (n - 2 >= kTracedLevels - 1 && !(rgb && !b.half)) {  // T_{n-1} is rebuilt from T_{n-2}: merged levels only
+        if (n - 2 >= kTracedLevels - 1 && pair_down) {  // T_{n-1} is rebuilt from T_{n-2}: merged levels only
             n -= 2;
             p = fused(PH_FUSE_DOWN, n, 2);
             p.a.fu.R[0] = r_of(n);

@@ -34,7 +34,10 @@
 // sizes: the LDS of a top or four-level block (78 and 58 KB) leaves two on a CU,
 // so FP32 blocks of 1024 threads fill its 32 waves (512: 32 and 25.6 us); the
 // 16-bit ones fit three to five (1024: 30.5 and 23.8 us, 512: 28.2 and 20.4), and
-// a merge down four (512 threads: 24.0 and 24.8 us, 256: 24.0 and 22.6).
+// a merge down four (512 threads: 24.0 and 24.8 us, 256: 24.0 and 22.6).  RGB
+// intervals take twice the LDS, so twice the threads fill the chip again: merges
+// up 85.5 -> 81.5 us, top 40.6 -> 37, a merge down 97 -> 81 to 86, one adjoint of two
+// levels at 512^2 21.4 -> 17.5.
 //
 // The arithmetic of every element, and its order, is that of the
 // level-by-level bodies, and 16-bit intervals are rounded at the same points
@@ -395,7 +398,8 @@ template <typename TS, int V, int L, int NT, int COLS> struct TnLoad {
 // level with a destination in a.T is stored (the last one always).
 template <typename TS, int G> struct FuseUp {
     static constexpr int L = kWindow, V = sizeof(TS) == 16 ? 1 : 2, H = L / (64 * V);
-    static constexpr int NT = G == 2 ? 256 : G == 3 || sizeof(TS) == 4 ? 512 : 1024, NW = NT / 64;
+    static constexpr int NT = (G == 2 ? 256 : G == 3 || sizeof(TS) == 4 ? 512 : 1024) << (sizeof(TS) == 16);
+    static constexpr int NW = NT / 64;
     static constexpr int win = L - (2 << G);  // 2 (2^G - 1) rows of halo
     static constexpr int rows(int j) { return (1 << (G - j)) * ((1 << j) + 1); }
     static constexpr int region(int p) {
@@ -486,7 +490,7 @@ __device__ __forceinline__ void fuse_up_block(const FuseArgs &a, char *lds, int 
 template <typename TS, int M> struct FuseTop {
     static constexpr int L = kWindow, ch = Store<TS>::ch;
     static constexpr int V = sizeof(TS) == 16 ? 1 : 2, H = L / (64 * V);
-    static constexpr int NT = M == 4 && sizeof(TS) == 8 ? 1024 : 512, NW = NT / 64;
+    static constexpr int NT = (M == 4 && sizeof(TS) == 8) || sizeof(TS) == 16 ? 1024 : 512, NW = NT / 64;
     static constexpr int win = L - 2 * ((1 << M) - 1);  // halo: from column 1 to the far edge
     static constexpr int cols(int j) { return (1 << (M - j)) - 1; }
     static constexpr int t_rows(int j) { return cols(j) * ((1 << j) + 1); }
@@ -676,7 +680,7 @@ __device__ __forceinline__ void fuse_top_block(const FuseArgs &a, char *lds, int
 // (R_{n+2} waits for its place in registers).
 template <typename TS> struct FuseDown {
     static constexpr int L = kWindow, V = sizeof(TS) == 16 ? 1 : 2, H = L / (64 * V);
-    static constexpr int NT = 256, NW = NT / 64, ch = Store<TS>::ch;
+    static constexpr int ch = Store<TS>::ch, NT = ch == 3 ? 512 : 256, NW = NT / 64;
     static constexpr int CC = sizeof(TS) == 16 ? 4 : 8;
     // R_n looks up to 4 rows into R_{n+1}, that up to 8 into R_{n+2}: six columns on
     static constexpr int win = L - 12;
@@ -870,7 +874,8 @@ __device__ __forceinline__ void fuse_down_block(const FuseArgs &a, char *lds, in
 // Lookups run down the window, at most 4 + 8 rows, so the first 12 rows of a
 // window hold no valid results.
 template <typename TS> struct FuseDr {
-    static constexpr int L = kWindow, V = 2, NT = 256, NW = NT / 64, ch = Store<TS>::ch;
+    static constexpr int L = kWindow, V = 2, ch = Store<TS>::ch;
+    static constexpr int NT = ch == 3 ? 512 : 256, NW = NT / 64;
     static constexpr int CC = 8, win = L - 12, skip = 12;
     static constexpr int d0_cols = CC + 5, t0_cols = CC + 4, t1_cols = 4, d1_cols = CC / 2 + 2;
     static constexpr int pad = 16;  // floats before the first row
