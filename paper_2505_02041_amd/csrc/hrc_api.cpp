@@ -195,9 +195,9 @@ static int build_fused_merges(const Ws &w, const SolveBuffers &b, bool keep, boo
     };
     Phase p;
     // RGB in FP32 merges down two levels at a time where that saves storing the
-    // levels between and the grid is past the caches: at 1024^2 81 and 86 us a
-    // pair against 73 and 82, but the merges up before it 82 against 107; at 512^2
-    // (two levels 25 against 17) it would not
+    // levels between and the grid is past the caches: at 1024^2 71 and 76 us a
+    // pair against 73 and 82, and the merges up before it 82 against 107; at 512^2
+    // (a pair 25 against 17) it would not
     const bool pair_down = !rgb || b.half || (!keep && N >= 10);
     const int max_up = rgb ? 3 : 4;
     for (int n = kTracedLevels - 1; n < n_top;) {

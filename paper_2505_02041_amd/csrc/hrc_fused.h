@@ -36,8 +36,11 @@
 // 16-bit ones fit three to five (1024: 30.5 and 23.8 us, 512: 28.2 and 20.4), and
 // a merge down four (512 threads: 24.0 and 24.8 us, 256: 24.0 and 22.6).  RGB
 // intervals take twice the LDS, so twice the threads fill the chip again: merges
-// up 85.5 -> 81.5 us, top 40.6 -> 37, a merge down 97 -> 81 to 86, one adjoint of two
-// levels at 512^2 21.4 -> 17.5.
+// up 85.5 -> 81.5 us, top 40.6 -> 37, one adjoint of two levels at 512^2 21.4 -> 17.5.
+// Its merge down has 10 or 12 items per level: 12 waves take one each (256 threads: 97
+// us, 512: 81 and 86, 768: 71 and 76, 1024: 76 and 82).  Wave counts that are no
+// multiple of the CU's four SIMDs lose more than they save (one channel down:
+// 256 threads 23 us, 320: 28.6, 384: 28.0).
 //
 // The arithmetic of every element, and its order, is that of the
 // level-by-level bodies, and 16-bit intervals are rounded at the same points
@@ -680,7 +683,7 @@ __device__ __forceinline__ void fuse_top_block(const FuseArgs &a, char *lds, int
 // (R_{n+2} waits for its place in registers).
 template <typename TS> struct FuseDown {
     static constexpr int L = kWindow, V = sizeof(TS) == 16 ? 1 : 2, H = L / (64 * V);
-    static constexpr int ch = Store<TS>::ch, NT = ch == 3 ? 512 : 256, NW = NT / 64;
+    static constexpr int ch = Store<TS>::ch, NT = ch == 3 ? 768 : 256, NW = NT / 64;
     static constexpr int CC = sizeof(TS) == 16 ? 4 : 8;
     // R_n looks up to 4 rows into R_{n+1}, that up to 8 into R_{n+2}: six columns on
     static constexpr int win = L - 12;
