@@ -28,9 +28,9 @@
 // Measured at 1024^2 (FP32, four quadrants, per forward): T_2 -> T_4, T_6 23.2 us
 // (four single levels 40), 107 MB at 4.6 TB/s; T_6 -> R_6 28.5 us (three levels up
 // and four down: 76), bound by vector and scalar issue (35 and 40 thousand
-// instructions a CU in 58 thousand cycles); R_6 -> R_4 -> R_2 24 us each (two
+// instructions a CU in 58 thousand cycles); R_6 -> R_4 -> R_2 20.9 us each (two
 // single levels 24, but those need T_3 and T_5 stored), 67 MB, half HBM and half
-// issue.  Forward 217.7 -> 133 us, 64^2 37 -> 24 us (3 launches for 11).  Block
+// issue.  Forward 217.7 -> 119 us, 64^2 37 -> 24 us (3 launches for 11).  Block
 // sizes: the LDS of a top or four-level block (78 and 58 KB) leaves two on a CU,
 // so FP32 blocks of 1024 threads fill its 32 waves (512: 32 and 25.6 us); the
 // 16-bit ones fit three to five (1024: 30.5 and 23.8 us, 512: 28.2 and 20.4), and
@@ -757,10 +757,18 @@ __device__ __forceinline__ void fuse_down_levels(const FuseArgs &a, const FuseTi
     auto t1_col = [&](int i) { return t1 + (i - 1) * 3 * L; };
     auto r2_col = [&](int i) { return r2 + (i - 1) * 4 * CH * L; };
     auto r1_col = [&](int i) { return r1 + (i - 1) * 2 * CH * L; };
+    // A wave's items at the levels with two cones: one row part h and cone k, and
+    // every DX-th column from xw; the unrolled loops then address by immediates and a
+    // column's parity is the wave's (22.3 -> 20.9 us a pair).
+    constexpr int DX = NW / (2 * H), IX = (F::c1 + DX - 1) / DX;
+    static_assert(NW % (2 * H) == 0, "waves");
+    const int h = wave % H, k = wave / H & 1, xw = 1 + wave / (2 * H);
+    const Rows<V> w((h * 64 + lane) * V, t.y0, sb, S);
     // T_{n+1}: directions 0, 1 and direction 2 of every column
-    for (int i = wave; i < F::c1 * 2 * H; i += NW) {
-        const int h = i % H, e = i / H, X = 1 + (e >> 1), k = e & 1;
-        const Rows<V> w((h * 64 + lane) * V, t.y0, sb, S);
+#pragma unroll
+    for (int it = 0; it < IX; ++it) {
+        const int X = xw + DX * it;
+        if (X > F::c1) break;
         const int far = (int)(t0_col(2 * X + 1) - t0_col(2 * X));
         C ev[V], od[V];
         fused_up<TS, V, L, true, IN>(t0_col(2 * X) + k * L + w.r, far, k, w, w.y(2 * X - 1) + sb, ev, od);
@@ -774,12 +782,13 @@ __device__ __forceinline__ void fuse_down_levels(const FuseArgs &a, const FuseTi
         __syncthreads();
     }
     // R_{n+1}
-    for (int i = wave; i < F::c1 * 2 * H; i += NW) {
-        const int h = i % H, e = i / H, x = 1 + (e >> 1), k = e & 1;
-        if ((x0 >> 1) + x >= (cols >> 1)) continue;  // beyond the grid: read by no one
-        const Rows<V> w((h * 64 + lane) * V, t.y0, sb, S);
+    const float4 wt1 = wl[1 + k];
+#pragma unroll
+    for (int it = 0; it < IX; ++it) {
+        const int x = xw + DX * it;
+        if (x > F::c1 || (x0 >> 1) + x >= (cols >> 1)) break;  // beyond the grid: read by no one
         const int y = w.y(2 * x - 1);
-        const float4 wt = wl[1 + k];
+        const float4 wt = wt1;
         const int c = (x + 1) >> 1;
         float o[CH][V];
         if (x & 1) {
@@ -811,12 +820,15 @@ __device__ __forceinline__ void fuse_down_levels(const FuseArgs &a, const FuseTi
     }
     __syncthreads();
     // R_n
-    for (int i = wave; i < CC * H; i += NW) {
-        const int h = i % H, x = 1 + i / H;
-        if (x0 + x >= cols) continue;
-        const Rows<V> w((h * 64 + lane) * V, t.y0, sb, S);
+    const float4 wt0 = wl[0];
+    // (not unrolled: its stores then came in one burst at the end, 25 us more a
+    // pair at 4096^2)
+#pragma unroll 1
+    for (int it = 0; it < (CC * H + NW - 1) / NW; ++it) {
+        const int x = 1 + wave / H + NW / H * it;
+        if (x > CC || x0 + x >= cols) break;
         const int y = w.y(x - 1);
-        const float4 wt = wl[0];
+        const float4 wt = wt0;
         const int c = (x + 1) >> 1;
         float o[CH][V];
         if (x & 1) {
