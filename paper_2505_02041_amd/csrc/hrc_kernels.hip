@@ -865,10 +865,160 @@ __device__ __forceinline__ float r2_at(const float *R2, int ro, int jj, int y, i
     return in ? v : fill;
 }
 
-template <int TILE, bool KEEP>
-__device__ __forceinline__ void body_tail(const TailArgs &a, unsigned tile, char *lds, int tid) {
+// One quadrant of a tile (Q < 0: given at run time).  With the quadrant known the
+// steps su, sw are constants and every LDS offset an immediate: 512^2 (16-pixel
+// tiles) 11.8 -> 10.8 us, 1024^2 21.2 -> 20.7.  What remains is the rays' and cones'
+// arithmetic (35 thousand vector instructions a CU in 42 thousand cycles at 1024^2).
+// The persistent batch keeps one body for the four (its kernels are short of
+// registers).
+template <int TILE, bool KEEP, int Q>
+__device__ __forceinline__ void tail_quadrant(const TailArgs &a, int g, int r0, int c0,
+                                              const float2 *iv, float *r1, float *acc, int tid) {
     using G = TailTile<TILE>;
     constexpr int H = G::halo, P = G::pitch, RR = G::r1rows, AP = G::acc_pitch;
+    const int N = a.N, S = 1 << N, q = Q < 0 ? a.q0 + g : Q;
+    // (else the offsets of all four quadrants are hoisted out of the loop: 256 registers)
+    if constexpr (Q >= 0) asm volatile("" : "+v"(tid));
+    const float *R2 = a.R2 + (size_t)g * S * S;
+    float *R1 = KEEP ? a.R1 + (size_t)g * S * S : nullptr;
+    const float *envq = a.env ? a.env + (size_t)q * kConeTable : nullptr;
+    // angular fluences beyond the grid (uniform over the tile)
+    const float e10 = env_fluence(envq, 1, 0), e11 = env_fluence(envq, 1, 1);
+    const float e20 = env_fluence(envq, 2, 0), e21 = env_fluence(envq, 2, 1);
+    const float e22 = env_fluence(envq, 2, 2), e23 = env_fluence(envq, 2, 3);
+    // frame of quadrant q: +x (u, w) = (c, r); -x (S-1-c, r); +y (r, c); -y (S-1-r, c);
+    // the tile covers u_lo .. u_lo + TILE - 1, w_lo .. w_lo + TILE - 1, and
+    // frame pixel (u, w) sits at LDS index base + (u - u_lo) su + (w - w_lo) sw
+    const int u_lo = q == 0 ? c0 : q == 1 ? S - TILE - c0 : q == 2 ? r0 : S - TILE - r0;
+    const int w_lo = q < 2 ? r0 : c0;
+    const int su = q == 0 ? 1 : q == 1 ? -1 : q == 2 ? P : -P;
+    const int sw = q < 2 ? P : 1;
+    const int base = q == 1 ? H * P + TILE - 1 + H : q == 3 ? (TILE - 1 + H) * P + H : H * P + H;
+    const int c1_lo = u_lo / 2 + 1;  // u_lo is even, so the first level-1 column is odd
+    const int cmax = S >> 2;          // level-2 columns in the grid
+    __syncthreads();  // intervals and sums in place; the previous quadrant's R_1 consumed
+    // R_1 at odd level-1 columns (Eq. 14 at level 1, through T_1)
+    constexpr int n_odd = (TILE / 4 + 1) * RR;
+#pragma unroll
+    for (int it = 0; it < (n_odd + 255) / 256; ++it) {
+        const int i = tid + 256 * it;
+        if (i >= n_odd) break;
+        const int j = 2 * (i / RR), wl = i % RR;
+        const int cp = c1_lo + j, w = w_lo - 2 + wl;
+        float v0 = e10, v1 = e11;
+        if (cp < 0) {
+            v0 = v1 = 0.f;
+        } else if (cp < (S >> 1) && (unsigned)w < (unsigned)S) {
+            const float2 *ivp = iv + base + (2 * cp - u_lo) * su + (w - w_lo) * sw;
+            const float2 t0 = tail_ray<2, 4, G::plane>(ivp, su, sw);
+            const float2 t1 = tail_ray<3, 4, G::plane>(ivp, su, sw);
+            const float2 t2 = tail_ray<4, 4, G::plane>(ivp, su, sw);
+            const int c = (cp + 1) >> 1;
+            const bool cin = c < cmax;
+            const int ro = (cin ? c : 0) * 4 * S;
+            v0 = fmaf(t0.y, r2_at(R2, ro, 0, w - 2, S, cin, e20), c_cone[3] * t0.x) +
+                 fmaf(t1.y, r2_at(R2, ro, 1, w, S, cin, e21), c_cone[4] * t1.x);
+            v1 = fmaf(t1.y, r2_at(R2, ro, 2, w, S, cin, e22), c_cone[5] * t1.x) +
+                 fmaf(t2.y, r2_at(R2, ro, 3, w + 2, S, cin, e23), c_cone[6] * t2.x);
+        }
+        r1[(2 * j) * RR + wl] = v0;
+        r1[(2 * j + 1) * RR + wl] = v1;
+        // the tile's own part of R_1, for the reverse (its last column is
+        // the next tile's first)
+        if (KEEP && j < TILE / 2 && cp > 0 && cp < (S >> 1) && (unsigned)(wl - 2) < (unsigned)TILE &&
+            (unsigned)w < (unsigned)S) {
+            R1[(unsigned)((2 * cp) << N) + (unsigned)w] = v0;
+            R1[(unsigned)((2 * cp + 1) << N) + (unsigned)w] = v1;
+        }
+    }
+    // R_1 at even level-1 columns (Eq. 15-17 at level 1, through the even directions of T_2)
+    constexpr int n_even = (TILE / 4) * RR;
+#pragma unroll
+    for (int it = 0; it < (n_even + 255) / 256; ++it) {
+        const int i = tid + 256 * it;
+        if (i >= n_even) break;
+        const int j = 2 * (i / RR) + 1, wl = i % RR;
+        const int cp = c1_lo + j, w = w_lo - 2 + wl;
+        float v0 = e10, v1 = e11;
+        if (cp < 0) {
+            v0 = v1 = 0.f;
+        } else if (cp < (S >> 1) && (unsigned)w < (unsigned)S) {
+            const float2 *ivp = iv + base + (2 * cp - u_lo) * su + (w - w_lo) * sw;
+            const float2 t0 = tail_ray<5, 8, G::plane>(ivp, su, sw);
+            const float2 t2 = tail_ray<7, 8, G::plane>(ivp, su, sw);
+            const float2 t4 = tail_ray<9, 8, G::plane>(ivp, su, sw);
+            const int c = cp >> 1;  // < cmax: cp < S / 2
+            const bool cin = c + 1 < cmax;
+            const int ro = c * 4 * S, ro1 = (cin ? c + 1 : 0) * 4 * S;
+            v0 = 0.5f * (r2_at(R2, ro, 0, w, S, true, e20) +
+                         fmaf(t0.y, r2_at(R2, ro1, 0, w - 4, S, cin, e20), c_cone[3] * t0.x)) +
+                 0.5f * (r2_at(R2, ro, 1, w, S, true, e21) +
+                         fmaf(t2.y, r2_at(R2, ro1, 1, w, S, cin, e21), c_cone[4] * t2.x));
+            v1 = 0.5f * (r2_at(R2, ro, 2, w, S, true, e22) +
+                         fmaf(t2.y, r2_at(R2, ro1, 2, w, S, cin, e22), c_cone[5] * t2.x)) +
+                 0.5f * (r2_at(R2, ro, 3, w, S, true, e23) +
+                         fmaf(t4.y, r2_at(R2, ro1, 3, w + 4, S, cin, e23), c_cone[6] * t4.x));
+        }
+        r1[(2 * j) * RR + wl] = v0;
+        r1[(2 * j + 1) * RR + wl] = v1;
+        if (KEEP && cp > 0 && cp < (S >> 1) && (unsigned)(wl - 2) < (unsigned)TILE &&
+            (unsigned)w < (unsigned)S) {
+            R1[(unsigned)((2 * cp) << N) + (unsigned)w] = v0;
+            R1[(unsigned)((2 * cp + 1) << N) + (unsigned)w] = v1;
+        }
+    }
+    __syncthreads();
+    if (KEEP && !a.out) return;  // R_1 alone
+    // R_0 at x = u + 1 for every pixel (u, w) of the tile, added to the sum.
+    // A thread keeps its row w; its column offsets ul are all even (x
+    // odd) in the first half of the passes and all odd in the second, so
+    // each pass holds one parity of x for the whole block (with a single
+    // pass, for each wave).  Offsets into the intervals and the sum are
+    // linear in ul and wl.
+    constexpr int SP = 256 / TILE, IT = TILE * TILE / 256;
+    const int wl = tid % TILE, w = w_lo + wl, slot0 = tid / TILE;
+    const int au = q == 0 ? 1 : q == 1 ? -1 : q == 2 ? AP : -AP;
+    const int aw = q < 2 ? AP : 1;
+    const int abase = q == 1 ? TILE - 1 : q == 3 ? (TILE - 1) * AP : 0;
+    const float2 *ivw = iv + base + su + wl * sw;  // pixel (u_lo + 1, w)
+    float *accw = acc + abase + wl * aw;
+#pragma unroll
+    for (int it = 0; it < IT; ++it) {
+        int ul;
+        if constexpr (IT >= 2)
+            ul = 2 * (slot0 + SP * (it % (IT / 2))) + (it >= IT / 2 ? 1 : 0);
+        else
+            ul = slot0 < SP / 2 ? 2 * slot0 : 2 * (slot0 - SP / 2) + 1;
+        const int u = u_lo + ul;
+        if (u < 0 || u >= S || w >= S) continue;
+        const float2 *ivp = ivw + ul * su;  // the probe at x = u + 1
+        float v;
+        if ((ul & 1) == 0) {
+            // x odd, Eq. 14 at level 0: both directions of T_0, R_1 at the
+            // next level-1 probe (column (x + 1) / 2)
+            const float2 t0 = tail_ray<0, 2, G::plane>(ivp, su, sw);
+            const float2 t1 = tail_ray<1, 2, G::plane>(ivp, su, sw);
+            const float *rj = r1 + ul * RR + wl;
+            v = fmaf(t0.y, rj[1], c_cone[1] * t0.x) + fmaf(t1.y, rj[RR + 3], c_cone[2] * t1.x);
+        } else if (u + 1 < S) {
+            // x even, Eq. 15-17 at level 0: the co-located level-1 probe
+            // (column x / 2) and the doubled edges (directions 0 and 2 of T_1)
+            const float2 t0 = tail_ray<2, 4, G::plane>(ivp, su, sw);
+            const float2 t2 = tail_ray<4, 4, G::plane>(ivp, su, sw);
+            const float *rj = r1 + (ul - 1) * RR + wl;
+            v = 0.5f * (rj[2] + fmaf(t0.y, rj[2 * RR], c_cone[1] * t0.x)) +
+                0.5f * (rj[RR + 2] + fmaf(t2.y, rj[3 * RR + 4], c_cone[2] * t2.x));
+        } else {
+            v = env_fluence(envq, 0, 0);  // x = S: beyond the grid
+        }
+        accw[ul * au] += v;
+    }
+}
+
+template <int TILE, bool KEEP, bool QUADS>
+__device__ __forceinline__ void body_tail(const TailArgs &a, unsigned tile, char *lds, int tid) {
+    using G = TailTile<TILE>;
+    constexpr int H = G::halo, P = G::pitch, AP = G::acc_pitch;
     constexpr int span2 = G::span * G::span;
     float2 *iv = reinterpret_cast<float2 *>(lds);
     float *r1 = reinterpret_cast<float *>(lds + G::iv_bytes);
@@ -897,140 +1047,15 @@ __device__ __forceinline__ void body_tail(const TailArgs &a, unsigned tile, char
         acc[rl * AP + cl] = (a.accumulate && r < S && c < S) ? a.out[r * S + c] : 0.f;
     }
     for (int g = 0; g < a.nq; ++g) {
-        const int q = a.q0 + g;
-        const float *R2 = a.R2 + (size_t)g * S * S;
-        float *R1 = KEEP ? a.R1 + (size_t)g * S * S : nullptr;
-        const float *envq = a.env ? a.env + (size_t)q * kConeTable : nullptr;
-        // angular fluences beyond the grid (uniform over the tile)
-        const float e10 = env_fluence(envq, 1, 0), e11 = env_fluence(envq, 1, 1);
-        const float e20 = env_fluence(envq, 2, 0), e21 = env_fluence(envq, 2, 1);
-        const float e22 = env_fluence(envq, 2, 2), e23 = env_fluence(envq, 2, 3);
-        // frame of quadrant q: +x (u, w) = (c, r); -x (S-1-c, r); +y (r, c); -y (S-1-r, c);
-        // the tile covers u_lo .. u_lo + TILE - 1, w_lo .. w_lo + TILE - 1, and
-        // frame pixel (u, w) sits at LDS index base + (u - u_lo) su + (w - w_lo) sw
-        const int u_lo = q == 0 ? c0 : q == 1 ? S - TILE - c0 : q == 2 ? r0 : S - TILE - r0;
-        const int w_lo = q < 2 ? r0 : c0;
-        const int su = q == 0 ? 1 : q == 1 ? -1 : q == 2 ? P : -P;
-        const int sw = q < 2 ? P : 1;
-        const int base = q == 1 ? H * P + TILE - 1 + H : q == 3 ? (TILE - 1 + H) * P + H : H * P + H;
-        const int c1_lo = u_lo / 2 + 1;  // u_lo is even, so the first level-1 column is odd
-        const int cmax = S >> 2;          // level-2 columns in the grid
-        __syncthreads();  // intervals and sums in place; the previous quadrant's R_1 consumed
-        // R_1 at odd level-1 columns (Eq. 14 at level 1, through T_1)
-        constexpr int n_odd = (TILE / 4 + 1) * RR;
-#pragma unroll
-        for (int it = 0; it < (n_odd + 255) / 256; ++it) {
-            const int i = tid + 256 * it;
-            if (i >= n_odd) break;
-            const int j = 2 * (i / RR), wl = i % RR;
-            const int cp = c1_lo + j, w = w_lo - 2 + wl;
-            float v0 = e10, v1 = e11;
-            if (cp < 0) {
-                v0 = v1 = 0.f;
-            } else if (cp < (S >> 1) && (unsigned)w < (unsigned)S) {
-                const float2 *ivp = iv + base + (2 * cp - u_lo) * su + (w - w_lo) * sw;
-                const float2 t0 = tail_ray<2, 4, G::plane>(ivp, su, sw);
-                const float2 t1 = tail_ray<3, 4, G::plane>(ivp, su, sw);
-                const float2 t2 = tail_ray<4, 4, G::plane>(ivp, su, sw);
-                const int c = (cp + 1) >> 1;
-                const bool cin = c < cmax;
-                const int ro = (cin ? c : 0) * 4 * S;
-                v0 = fmaf(t0.y, r2_at(R2, ro, 0, w - 2, S, cin, e20), c_cone[3] * t0.x) +
-                     fmaf(t1.y, r2_at(R2, ro, 1, w, S, cin, e21), c_cone[4] * t1.x);
-                v1 = fmaf(t1.y, r2_at(R2, ro, 2, w, S, cin, e22), c_cone[5] * t1.x) +
-                     fmaf(t2.y, r2_at(R2, ro, 3, w + 2, S, cin, e23), c_cone[6] * t2.x);
-            }
-            r1[(2 * j) * RR + wl] = v0;
-            r1[(2 * j + 1) * RR + wl] = v1;
-            // the tile's own part of R_1, for the reverse (its last column is
-            // the next tile's first)
-            if (KEEP && j < TILE / 2 && cp > 0 && cp < (S >> 1) && (unsigned)(wl - 2) < (unsigned)TILE &&
-                (unsigned)w < (unsigned)S) {
-                R1[(unsigned)((2 * cp) << N) + (unsigned)w] = v0;
-                R1[(unsigned)((2 * cp + 1) << N) + (unsigned)w] = v1;
-            }
+        if constexpr (!QUADS) {
+            tail_quadrant<TILE, KEEP, -1>(a, g, r0, c0, iv, r1, acc, tid);
+            continue;
         }
-        // R_1 at even level-1 columns (Eq. 15-17 at level 1, through the even directions of T_2)
-        constexpr int n_even = (TILE / 4) * RR;
-#pragma unroll
-        for (int it = 0; it < (n_even + 255) / 256; ++it) {
-            const int i = tid + 256 * it;
-            if (i >= n_even) break;
-            const int j = 2 * (i / RR) + 1, wl = i % RR;
-            const int cp = c1_lo + j, w = w_lo - 2 + wl;
-            float v0 = e10, v1 = e11;
-            if (cp < 0) {
-                v0 = v1 = 0.f;
-            } else if (cp < (S >> 1) && (unsigned)w < (unsigned)S) {
-                const float2 *ivp = iv + base + (2 * cp - u_lo) * su + (w - w_lo) * sw;
-                const float2 t0 = tail_ray<5, 8, G::plane>(ivp, su, sw);
-                const float2 t2 = tail_ray<7, 8, G::plane>(ivp, su, sw);
-                const float2 t4 = tail_ray<9, 8, G::plane>(ivp, su, sw);
-                const int c = cp >> 1;  // < cmax: cp < S / 2
-                const bool cin = c + 1 < cmax;
-                const int ro = c * 4 * S, ro1 = (cin ? c + 1 : 0) * 4 * S;
-                v0 = 0.5f * (r2_at(R2, ro, 0, w, S, true, e20) +
-                             fmaf(t0.y, r2_at(R2, ro1, 0, w - 4, S, cin, e20), c_cone[3] * t0.x)) +
-                     0.5f * (r2_at(R2, ro, 1, w, S, true, e21) +
-                             fmaf(t2.y, r2_at(R2, ro1, 1, w, S, cin, e21), c_cone[4] * t2.x));
-                v1 = 0.5f * (r2_at(R2, ro, 2, w, S, true, e22) +
-                             fmaf(t2.y, r2_at(R2, ro1, 2, w, S, cin, e22), c_cone[5] * t2.x)) +
-                     0.5f * (r2_at(R2, ro, 3, w, S, true, e23) +
-                             fmaf(t4.y, r2_at(R2, ro1, 3, w + 4, S, cin, e23), c_cone[6] * t4.x));
-            }
-            r1[(2 * j) * RR + wl] = v0;
-            r1[(2 * j + 1) * RR + wl] = v1;
-            if (KEEP && cp > 0 && cp < (S >> 1) && (unsigned)(wl - 2) < (unsigned)TILE &&
-                (unsigned)w < (unsigned)S) {
-                R1[(unsigned)((2 * cp) << N) + (unsigned)w] = v0;
-                R1[(unsigned)((2 * cp + 1) << N) + (unsigned)w] = v1;
-            }
-        }
-        __syncthreads();
-        if (KEEP && !a.out) continue;  // R_1 alone
-        // R_0 at x = u + 1 for every pixel (u, w) of the tile, added to the sum.
-        // A thread keeps its row w; its column offsets ul are all even (x
-        // odd) in the first half of the passes and all odd in the second, so
-        // each pass holds one parity of x for the whole block (with a single
-        // pass, for each wave).  Offsets into the intervals and the sum are
-        // linear in ul and wl.
-        constexpr int SP = 256 / TILE, IT = TILE * TILE / 256;
-        const int wl = tid % TILE, w = w_lo + wl, slot0 = tid / TILE;
-        const int au = q == 0 ? 1 : q == 1 ? -1 : q == 2 ? AP : -AP;
-        const int aw = q < 2 ? AP : 1;
-        const int abase = q == 1 ? TILE - 1 : q == 3 ? (TILE - 1) * AP : 0;
-        const float2 *ivw = iv + base + su + wl * sw;  // pixel (u_lo + 1, w)
-        float *accw = acc + abase + wl * aw;
-#pragma unroll
-        for (int it = 0; it < IT; ++it) {
-            int ul;
-            if constexpr (IT >= 2)
-                ul = 2 * (slot0 + SP * (it % (IT / 2))) + (it >= IT / 2 ? 1 : 0);
-            else
-                ul = slot0 < SP / 2 ? 2 * slot0 : 2 * (slot0 - SP / 2) + 1;
-            const int u = u_lo + ul;
-            if (u < 0 || u >= S || w >= S) continue;
-            const float2 *ivp = ivw + ul * su;  // the probe at x = u + 1
-            float v;
-            if ((ul & 1) == 0) {
-                // x odd, Eq. 14 at level 0: both directions of T_0, R_1 at the
-                // next level-1 probe (column (x + 1) / 2)
-                const float2 t0 = tail_ray<0, 2, G::plane>(ivp, su, sw);
-                const float2 t1 = tail_ray<1, 2, G::plane>(ivp, su, sw);
-                const float *rj = r1 + ul * RR + wl;
-                v = fmaf(t0.y, rj[1], c_cone[1] * t0.x) + fmaf(t1.y, rj[RR + 3], c_cone[2] * t1.x);
-            } else if (u + 1 < S) {
-                // x even, Eq. 15-17 at level 0: the co-located level-1 probe
-                // (column x / 2) and the doubled edges (directions 0 and 2 of T_1)
-                const float2 t0 = tail_ray<2, 4, G::plane>(ivp, su, sw);
-                const float2 t2 = tail_ray<4, 4, G::plane>(ivp, su, sw);
-                const float *rj = r1 + (ul - 1) * RR + wl;
-                v = 0.5f * (rj[2] + fmaf(t0.y, rj[2 * RR], c_cone[1] * t0.x)) +
-                    0.5f * (rj[RR + 2] + fmaf(t2.y, rj[3 * RR + 4], c_cone[2] * t2.x));
-            } else {
-                v = env_fluence(envq, 0, 0);  // x = S: beyond the grid
-            }
-            accw[ul * au] += v;
+        switch (a.q0 + g) {
+            case 0: tail_quadrant<TILE, KEEP, 0>(a, g, r0, c0, iv, r1, acc, tid); break;
+            case 1: tail_quadrant<TILE, KEEP, 1>(a, g, r0, c0, iv, r1, acc, tid); break;
+            case 2: tail_quadrant<TILE, KEEP, 2>(a, g, r0, c0, iv, r1, acc, tid); break;
+            default: tail_quadrant<TILE, KEEP, 3>(a, g, r0, c0, iv, r1, acc, tid); break;
         }
     }
     __syncthreads();
@@ -2196,11 +2221,152 @@ __device__ __forceinline__ float r2_at3(const float *R2, int ro, int jj, int y, 
     return in ? v : 0.f;
 }
 
+// One quadrant of a tile, as tail_quadrant.
+template <int TILE, int q>
+__device__ __forceinline__ void tail_quadrant_rgb(const TailArgs &a, int g, int r0, int c0,
+                                                  const float4 *iv, float *r1, float *acc, int tid) {
+    using G1 = TailTile<TILE>;
+    using G = TailTileRgb<TILE>;
+    constexpr int H = G1::halo, P = G1::pitch, RR = G1::r1rows, AP = G1::acc_pitch;
+    constexpr int R1P = G::r1_plane, ACP = G::acc_plane;
+    const int N = a.N, S = 1 << N;
+    asm volatile("" : "+v"(tid));
+    const size_t SS = (size_t)S * S, R2plane = (size_t)a.nq * SS;
+    const float *R2 = a.R2 + (size_t)g * SS;
+    const int u_lo = q == 0 ? c0 : q == 1 ? S - TILE - c0 : q == 2 ? r0 : S - TILE - r0;
+    const int w_lo = q < 2 ? r0 : c0;
+    const int su = q == 0 ? 1 : q == 1 ? -1 : q == 2 ? P : -P;
+    const int sw = q < 2 ? P : 1;
+    const int base = q == 1 ? H * P + TILE - 1 + H : q == 3 ? (TILE - 1 + H) * P + H : H * P + H;
+    const int c1_lo = u_lo / 2 + 1;
+    const int cmax = S >> 2;
+    __syncthreads();
+    // R_1 at odd level-1 columns (Eq. 14 at level 1)
+    constexpr int n_odd = (TILE / 4 + 1) * RR;
+    for (int i = tid; i < n_odd; i += 256) {
+        const int j = 2 * (i / RR), wl = i % RR;
+        const int cp = c1_lo + j, w = w_lo - 2 + wl;
+        float v0[3] = {0.f, 0.f, 0.f}, v1[3] = {0.f, 0.f, 0.f};
+        if (cp >= 0 && cp < (S >> 1) && (unsigned)w < (unsigned)S) {
+            const float4 *ivp = iv + base + (2 * cp - u_lo) * su + (w - w_lo) * sw;
+            const float4 t0 = tail_ray<2, 4, G::plane>(ivp, su, sw);
+            const float4 t1 = tail_ray<3, 4, G::plane>(ivp, su, sw);
+            const float4 t2 = tail_ray<4, 4, G::plane>(ivp, su, sw);
+            const int c = (cp + 1) >> 1;
+            const bool cin = c < cmax;
+            const int ro = (cin ? c : 0) * 4 * S;
+#pragma unroll
+            for (int ch = 0; ch < 3; ++ch) {
+                const float *R2c = R2 + ch * R2plane;
+                v0[ch] = fmaf(t0.w, r2_at3(R2c, ro, 0, w - 2, S, cin), c_cone[3] * chan(t0, ch)) +
+                         fmaf(t1.w, r2_at3(R2c, ro, 1, w, S, cin), c_cone[4] * chan(t1, ch));
+                v1[ch] = fmaf(t1.w, r2_at3(R2c, ro, 2, w, S, cin), c_cone[5] * chan(t1, ch)) +
+                         fmaf(t2.w, r2_at3(R2c, ro, 3, w + 2, S, cin), c_cone[6] * chan(t2, ch));
+            }
+        }
+        const bool keep = a.R1 && j < TILE / 2 && cp > 0 && cp < (S >> 1) &&
+                          (unsigned)(wl - 2) < (unsigned)TILE && (unsigned)w < (unsigned)S;
+#pragma unroll
+        for (int ch = 0; ch < 3; ++ch) {
+            r1[ch * R1P + (2 * j) * RR + wl] = v0[ch];
+            r1[ch * R1P + (2 * j + 1) * RR + wl] = v1[ch];
+            if (keep) {  // the tile's own part of R_1, for the reverse
+                float *R1 = a.R1 + ch * R2plane + (size_t)g * SS;
+                R1[((size_t)(2 * cp) << N) + w] = v0[ch];
+                R1[((size_t)(2 * cp + 1) << N) + w] = v1[ch];
+            }
+        }
+    }
+    // R_1 at even level-1 columns (Eq. 15-17 at level 1)
+    constexpr int n_even = (TILE / 4) * RR;
+    for (int i = tid; i < n_even; i += 256) {
+        const int j = 2 * (i / RR) + 1, wl = i % RR;
+        const int cp = c1_lo + j, w = w_lo - 2 + wl;
+        float v0[3] = {0.f, 0.f, 0.f}, v1[3] = {0.f, 0.f, 0.f};
+        if (cp >= 0 && cp < (S >> 1) && (unsigned)w < (unsigned)S) {
+            const float4 *ivp = iv + base + (2 * cp - u_lo) * su + (w - w_lo) * sw;
+            const float4 t0 = tail_ray<5, 8, G::plane>(ivp, su, sw);
+            const float4 t2 = tail_ray<7, 8, G::plane>(ivp, su, sw);
+            const float4 t4 = tail_ray<9, 8, G::plane>(ivp, su, sw);
+            const int c = cp >> 1;
+            const bool cin = c + 1 < cmax;
+            const int ro = c * 4 * S, ro1 = (cin ? c + 1 : 0) * 4 * S;
+#pragma unroll
+            for (int ch = 0; ch < 3; ++ch) {
+                const float *R2c = R2 + ch * R2plane;
+                v0[ch] = 0.5f * (r2_at3(R2c, ro, 0, w, S, true) +
+                                 fmaf(t0.w, r2_at3(R2c, ro1, 0, w - 4, S, cin), c_cone[3] * chan(t0, ch))) +
+                         0.5f * (r2_at3(R2c, ro, 1, w, S, true) +
+                                 fmaf(t2.w, r2_at3(R2c, ro1, 1, w, S, cin), c_cone[4] * chan(t2, ch)));
+                v1[ch] = 0.5f * (r2_at3(R2c, ro, 2, w, S, true) +
+                                 fmaf(t2.w, r2_at3(R2c, ro1, 2, w, S, cin), c_cone[5] * chan(t2, ch))) +
+                         0.5f * (r2_at3(R2c, ro, 3, w, S, true) +
+                                 fmaf(t4.w, r2_at3(R2c, ro1, 3, w + 4, S, cin), c_cone[6] * chan(t4, ch)));
+            }
+        }
+        const bool keep = a.R1 && j < TILE / 2 && cp > 0 && cp < (S >> 1) &&
+                          (unsigned)(wl - 2) < (unsigned)TILE && (unsigned)w < (unsigned)S;
+#pragma unroll
+        for (int ch = 0; ch < 3; ++ch) {
+            r1[ch * R1P + (2 * j) * RR + wl] = v0[ch];
+            r1[ch * R1P + (2 * j + 1) * RR + wl] = v1[ch];
+            if (keep) {  // the tile's own part of R_1, for the reverse
+                float *R1 = a.R1 + ch * R2plane + (size_t)g * SS;
+                R1[((size_t)(2 * cp) << N) + w] = v0[ch];
+                R1[((size_t)(2 * cp + 1) << N) + w] = v1[ch];
+            }
+        }
+    }
+    __syncthreads();
+    if (!a.out) return;  // R_1 alone
+    // R_0 at x = u + 1 for every pixel (u, w) of the tile, added to the sums
+    constexpr int SP = 256 / TILE, IT = TILE * TILE / 256;
+    const int wl = tid % TILE, w = w_lo + wl, slot0 = tid / TILE;
+    const int au = q == 0 ? 1 : q == 1 ? -1 : q == 2 ? AP : -AP;
+    const int aw = q < 2 ? AP : 1;
+    const int abase = q == 1 ? TILE - 1 : q == 3 ? (TILE - 1) * AP : 0;
+    const float4 *ivw = iv + base + su + wl * sw;
+    float *accw = acc + abase + wl * aw;
+#pragma unroll
+    for (int it = 0; it < IT; ++it) {
+        int ul;
+        if constexpr (IT >= 2)
+            ul = 2 * (slot0 + SP * (it % (IT / 2))) + (it >= IT / 2 ? 1 : 0);
+        else
+            ul = slot0 < SP / 2 ? 2 * slot0 : 2 * (slot0 - SP / 2) + 1;
+        const int u = u_lo + ul;
+        if (u < 0 || u >= S || w >= S) continue;
+        const float4 *ivp = ivw + ul * su;
+        float v[3] = {0.f, 0.f, 0.f};
+        if ((ul & 1) == 0) {
+            const float4 t0 = tail_ray<0, 2, G::plane>(ivp, su, sw);
+            const float4 t1 = tail_ray<1, 2, G::plane>(ivp, su, sw);
+#pragma unroll
+            for (int ch = 0; ch < 3; ++ch) {
+                const float *rj = r1 + ch * R1P + ul * RR + wl;
+                v[ch] = fmaf(t0.w, rj[1], c_cone[1] * chan(t0, ch)) +
+                        fmaf(t1.w, rj[RR + 3], c_cone[2] * chan(t1, ch));
+            }
+        } else if (u + 1 < S) {
+            const float4 t0 = tail_ray<2, 4, G::plane>(ivp, su, sw);
+            const float4 t2 = tail_ray<4, 4, G::plane>(ivp, su, sw);
+#pragma unroll
+            for (int ch = 0; ch < 3; ++ch) {
+                const float *rj = r1 + ch * R1P + (ul - 1) * RR + wl;
+                v[ch] = 0.5f * (rj[2] + fmaf(t0.w, rj[2 * RR], c_cone[1] * chan(t0, ch))) +
+                        0.5f * (rj[RR + 2] + fmaf(t2.w, rj[3 * RR + 4], c_cone[2] * chan(t2, ch)));
+            }
+        }
+#pragma unroll
+        for (int ch = 0; ch < 3; ++ch) accw[ch * ACP + ul * au] += v[ch];
+    }
+}
+
 template <int TILE>
 __device__ void body_tail_rgb(const TailArgs &a, unsigned tile, char *lds, int tid) {
     using G1 = TailTile<TILE>;
     using G = TailTileRgb<TILE>;
-    constexpr int H = G1::halo, P = G1::pitch, RR = G1::r1rows, AP = G1::acc_pitch;
+    constexpr int H = G1::halo, P = G1::pitch, AP = G1::acc_pitch;
     constexpr int span2 = G1::span * G1::span;
     constexpr int R1P = G::r1_plane, ACP = G::acc_plane;
     float4 *iv = reinterpret_cast<float4 *>(lds);
@@ -2221,138 +2387,13 @@ __device__ void body_tail_rgb(const TailArgs &a, unsigned tile, char *lds, int t
         iv[G::plane + lr * P + lc] = cell_interval_rgb(e0, e1, e2, g, kH2);
     }
     for (int i = tid; i < 3 * ACP; i += 256) acc[i] = 0.f;
-    const size_t R2plane = (size_t)a.nq * SS;
-    for (int g = 0; g < a.nq; ++g) {
-        const int q = a.q0 + g;
-        const float *R2 = a.R2 + (size_t)g * SS;
-        const int u_lo = q == 0 ? c0 : q == 1 ? S - TILE - c0 : q == 2 ? r0 : S - TILE - r0;
-        const int w_lo = q < 2 ? r0 : c0;
-        const int su = q == 0 ? 1 : q == 1 ? -1 : q == 2 ? P : -P;
-        const int sw = q < 2 ? P : 1;
-        const int base = q == 1 ? H * P + TILE - 1 + H : q == 3 ? (TILE - 1 + H) * P + H : H * P + H;
-        const int c1_lo = u_lo / 2 + 1;
-        const int cmax = S >> 2;
-        __syncthreads();
-        // R_1 at odd level-1 columns (Eq. 14 at level 1)
-        constexpr int n_odd = (TILE / 4 + 1) * RR;
-        for (int i = tid; i < n_odd; i += 256) {
-            const int j = 2 * (i / RR), wl = i % RR;
-            const int cp = c1_lo + j, w = w_lo - 2 + wl;
-            float v0[3] = {0.f, 0.f, 0.f}, v1[3] = {0.f, 0.f, 0.f};
-            if (cp >= 0 && cp < (S >> 1) && (unsigned)w < (unsigned)S) {
-                const float4 *ivp = iv + base + (2 * cp - u_lo) * su + (w - w_lo) * sw;
-                const float4 t0 = tail_ray<2, 4, G::plane>(ivp, su, sw);
-                const float4 t1 = tail_ray<3, 4, G::plane>(ivp, su, sw);
-                const float4 t2 = tail_ray<4, 4, G::plane>(ivp, su, sw);
-                const int c = (cp + 1) >> 1;
-                const bool cin = c < cmax;
-                const int ro = (cin ? c : 0) * 4 * S;
-#pragma unroll
-                for (int ch = 0; ch < 3; ++ch) {
-                    const float *R2c = R2 + ch * R2plane;
-                    v0[ch] = fmaf(t0.w, r2_at3(R2c, ro, 0, w - 2, S, cin), c_cone[3] * chan(t0, ch)) +
-                             fmaf(t1.w, r2_at3(R2c, ro, 1, w, S, cin), c_cone[4] * chan(t1, ch));
-                    v1[ch] = fmaf(t1.w, r2_at3(R2c, ro, 2, w, S, cin), c_cone[5] * chan(t1, ch)) +
-                             fmaf(t2.w, r2_at3(R2c, ro, 3, w + 2, S, cin), c_cone[6] * chan(t2, ch));
-                }
-            }
-            const bool keep = a.R1 && j < TILE / 2 && cp > 0 && cp < (S >> 1) &&
-                              (unsigned)(wl - 2) < (unsigned)TILE && (unsigned)w < (unsigned)S;
-#pragma unroll
-            for (int ch = 0; ch < 3; ++ch) {
-                r1[ch * R1P + (2 * j) * RR + wl] = v0[ch];
-                r1[ch * R1P + (2 * j + 1) * RR + wl] = v1[ch];
-                if (keep) {  // the tile's own part of R_1, for the reverse
-                    float *R1 = a.R1 + ch * R2plane + (size_t)g * SS;
-                    R1[((size_t)(2 * cp) << N) + w] = v0[ch];
-                    R1[((size_t)(2 * cp + 1) << N) + w] = v1[ch];
-                }
-            }
+    for (int g = 0; g < a.nq; ++g)
+        switch (a.q0 + g) {
+            case 0: tail_quadrant_rgb<TILE, 0>(a, g, r0, c0, iv, r1, acc, tid); break;
+            case 1: tail_quadrant_rgb<TILE, 1>(a, g, r0, c0, iv, r1, acc, tid); break;
+            case 2: tail_quadrant_rgb<TILE, 2>(a, g, r0, c0, iv, r1, acc, tid); break;
+            default: tail_quadrant_rgb<TILE, 3>(a, g, r0, c0, iv, r1, acc, tid); break;
         }
-        // R_1 at even level-1 columns (Eq. 15-17 at level 1)
-        constexpr int n_even = (TILE / 4) * RR;
-        for (int i = tid; i < n_even; i += 256) {
-            const int j = 2 * (i / RR) + 1, wl = i % RR;
-            const int cp = c1_lo + j, w = w_lo - 2 + wl;
-            float v0[3] = {0.f, 0.f, 0.f}, v1[3] = {0.f, 0.f, 0.f};
-            if (cp >= 0 && cp < (S >> 1) && (unsigned)w < (unsigned)S) {
-                const float4 *ivp = iv + base + (2 * cp - u_lo) * su + (w - w_lo) * sw;
-                const float4 t0 = tail_ray<5, 8, G::plane>(ivp, su, sw);
-                const float4 t2 = tail_ray<7, 8, G::plane>(ivp, su, sw);
-                const float4 t4 = tail_ray<9, 8, G::plane>(ivp, su, sw);
-                const int c = cp >> 1;
-                const bool cin = c + 1 < cmax;
-                const int ro = c * 4 * S, ro1 = (cin ? c + 1 : 0) * 4 * S;
-#pragma unroll
-                for (int ch = 0; ch < 3; ++ch) {
-                    const float *R2c = R2 + ch * R2plane;
-                    v0[ch] = 0.5f * (r2_at3(R2c, ro, 0, w, S, true) +
-                                     fmaf(t0.w, r2_at3(R2c, ro1, 0, w - 4, S, cin), c_cone[3] * chan(t0, ch))) +
-                             0.5f * (r2_at3(R2c, ro, 1, w, S, true) +
-                                     fmaf(t2.w, r2_at3(R2c, ro1, 1, w, S, cin), c_cone[4] * chan(t2, ch)));
-                    v1[ch] = 0.5f * (r2_at3(R2c, ro, 2, w, S, true) +
-                                     fmaf(t2.w, r2_at3(R2c, ro1, 2, w, S, cin), c_cone[5] * chan(t2, ch))) +
-                             0.5f * (r2_at3(R2c, ro, 3, w, S, true) +
-                                     fmaf(t4.w, r2_at3(R2c, ro1, 3, w + 4, S, cin), c_cone[6] * chan(t4, ch)));
-                }
-            }
-            const bool keep = a.R1 && j < TILE / 2 && cp > 0 && cp < (S >> 1) &&
-                              (unsigned)(wl - 2) < (unsigned)TILE && (unsigned)w < (unsigned)S;
-#pragma unroll
-            for (int ch = 0; ch < 3; ++ch) {
-                r1[ch * R1P + (2 * j) * RR + wl] = v0[ch];
-                r1[ch * R1P + (2 * j + 1) * RR + wl] = v1[ch];
-                if (keep) {  // the tile's own part of R_1, for the reverse
-                    float *R1 = a.R1 + ch * R2plane + (size_t)g * SS;
-                    R1[((size_t)(2 * cp) << N) + w] = v0[ch];
-                    R1[((size_t)(2 * cp + 1) << N) + w] = v1[ch];
-                }
-            }
-        }
-        __syncthreads();
-        if (!a.out) continue;  // R_1 alone
-        // R_0 at x = u + 1 for every pixel (u, w) of the tile, added to the sums
-        constexpr int SP = 256 / TILE, IT = TILE * TILE / 256;
-        const int wl = tid % TILE, w = w_lo + wl, slot0 = tid / TILE;
-        const int au = q == 0 ? 1 : q == 1 ? -1 : q == 2 ? AP : -AP;
-        const int aw = q < 2 ? AP : 1;
-        const int abase = q == 1 ? TILE - 1 : q == 3 ? (TILE - 1) * AP : 0;
-        const float4 *ivw = iv + base + su + wl * sw;
-        float *accw = acc + abase + wl * aw;
-#pragma unroll
-        for (int it = 0; it < IT; ++it) {
-            int ul;
-            if constexpr (IT >= 2)
-                ul = 2 * (slot0 + SP * (it % (IT / 2))) + (it >= IT / 2 ? 1 : 0);
-            else
-                ul = slot0 < SP / 2 ? 2 * slot0 : 2 * (slot0 - SP / 2) + 1;
-            const int u = u_lo + ul;
-            if (u < 0 || u >= S || w >= S) continue;
-            const float4 *ivp = ivw + ul * su;
-            float v[3] = {0.f, 0.f, 0.f};
-            if ((ul & 1) == 0) {
-                const float4 t0 = tail_ray<0, 2, G::plane>(ivp, su, sw);
-                const float4 t1 = tail_ray<1, 2, G::plane>(ivp, su, sw);
-#pragma unroll
-                for (int ch = 0; ch < 3; ++ch) {
-                    const float *rj = r1 + ch * R1P + ul * RR + wl;
-                    v[ch] = fmaf(t0.w, rj[1], c_cone[1] * chan(t0, ch)) +
-                            fmaf(t1.w, rj[RR + 3], c_cone[2] * chan(t1, ch));
-                }
-            } else if (u + 1 < S) {
-                const float4 t0 = tail_ray<2, 4, G::plane>(ivp, su, sw);
-                const float4 t2 = tail_ray<4, 4, G::plane>(ivp, su, sw);
-#pragma unroll
-                for (int ch = 0; ch < 3; ++ch) {
-                    const float *rj = r1 + ch * R1P + (ul - 1) * RR + wl;
-                    v[ch] = 0.5f * (rj[2] + fmaf(t0.w, rj[2 * RR], c_cone[1] * chan(t0, ch))) +
-                            0.5f * (rj[RR + 2] + fmaf(t2.w, rj[3 * RR + 4], c_cone[2] * chan(t2, ch)));
-                }
-            }
-#pragma unroll
-            for (int ch = 0; ch < 3; ++ch) accw[ch * ACP + ul * au] += v[ch];
-        }
-    }
     __syncthreads();
     if (!a.out) return;
     for (int i = tid; i < TILE * TILE; i += 256) {
@@ -2825,7 +2866,7 @@ __device__ __forceinline__ void run_phase(const Phase &p, unsigned tile, char *l
         case PH_SEED: body_seed<16, float2>(p.a.seed, tile, lds, tid); break;  // planner sets tile 16
         case PH_UP: body_merge_up<float2>(p.a.up, tile, p.U, tid); break;
         case PH_DOWN: body_merge_down<float2>(p.a.down, tile, p.U, tid); break;
-        case PH_TAIL: body_tail<16, false>(p.a.tail, tile, lds, tid); break;  // planner sets tile 16
+        case PH_TAIL: body_tail<16, false, false>(p.a.tail, tile, lds, tid); break;  // planner sets tile 16
         case PH_GATHER_ADJ: body_gather_adj(p.a.ga, tile, lds, tid); break;
         case PH_DOWN_ADJ: body_merge_down_adj<float2>(p.a.da, tile, p.U, tid); break;
         case PH_DT: body_dT<float2>(p.a.dt, tile, p.U, tid); break;
@@ -2879,7 +2920,7 @@ __global__ __launch_bounds__(256) void hrc_blur_adj(Phase p) {
 }
 template <int TILE, bool KEEP> __global__ __launch_bounds__(256) void hrc_tail(Phase p) {
     __shared__ __align__(16) char lds[TailTile<TILE>::lds];
-    body_tail<TILE, KEEP>(p.a.tail, xcd_tile(blockIdx.x, gridDim.x), lds, ltid());
+    body_tail<TILE, KEEP, true>(p.a.tail, xcd_tile(blockIdx.x, gridDim.x), lds, ltid());
 }
 __global__ __launch_bounds__(256) void hrc_seed_rgb(Phase p) {
     __shared__ __align__(16) char lds[SeedTileRgb<16>::lds];
