@@ -46,9 +46,9 @@ def parse():
 def measured_traffic(kernel: str):
     """HBM bytes per launch of `kernel` from the committed FETCH_SIZE/WRITE_SIZE
     profile (scaled by the plain-copy calibration), or None when there is no
-    such profile or the kernel source has changed since it was taken."""
+    such profile of it or the kernel source has changed since it was taken."""
     import hashlib
-    path = os.path.join(ROOT, "profiles", "hrc_merge_down_1024_traffic.json")
+    path = os.path.join(ROOT, "profiles", "hrc_forward_1024_traffic.json")
     if not os.path.exists(path):
         return None
     rec = json.load(open(path))
@@ -129,8 +129,9 @@ def main():
     import torch
     from paper_2505_02041_amd import Batch, Context
     from paper_2505_02041_amd import _lib
-    from paper_2505_02041_amd.roofline import (HBM_PEAK_GBPS, backward_bytes, forward_bytes,
-                                               forward_bytes_rgb, pass_bytes)
+    from paper_2505_02041_amd.roofline import (HBM_PEAK_GBPS, backward_bytes, backward_launches,
+                                               forward_bytes, forward_bytes_rgb,
+                                               forward_launches, group_launches)
     from scenes import config2, config3, config5
 
     def log(msg):
@@ -302,40 +303,38 @@ def main():
     del res
     ctx.release_workspaces()
 
-    # ---- per-pass kernel durations: the same launches as hrc_forward, each
-    # with HIP events the runtime records at the kernel's own start and end ---
-    log("per-pass kernel timing")
-    per = {}
+    # ---- kernel durations: the same launches as hrc_forward, each with HIP
+    # events the runtime records at the kernel's own start and end ------------
+    def kernel_times(launches, reps, *fields):
+        per = {}
+        for _ in range(reps):
+            rows = ctx.hrc_profile_solve(*fields)
+            for name, (c, ms, b) in group_launches(launches, rows).items():
+                c0, ms0, b0 = per.get(name, (0, 0.0, 0.0))
+                per[name] = (c0 + c, ms0 + ms, b0 + b)
+        return per
+
+    log("per-kernel timing")
     reps = max(5, args.steps // 2)
-    for _ in range(reps):
-        for name, n, ms in ctx.hrc_profile_solve(eps, sig):
-            tot_ms, tot_b, cnt = per.get(name, (0.0, 0.0, 0))
-            per[name] = (tot_ms + ms, tot_b + pass_bytes(name, N, n), cnt + 1)
-    dom = max(per, key=lambda k: per[k][0])
-    d_ms, d_b, d_cnt = per[dom]
+    per = kernel_times(forward_launches(N), reps, eps, sig)
+    kernel_name = max(per, key=lambda k: per[k][1])
+    d_cnt, d_ms, d_b = per[kernel_name]
     avg_launch_us = d_ms / d_cnt * 1e3
     bytes_per_launch = d_b / d_cnt
     achieved = bytes_per_launch / (avg_launch_us * 1e-6) / 1e9
-    passes = {k: {"launches_per_step": v[2] // reps, "ms_per_step": v[0] / reps,
-                  "GBps": v[1] / (v[0] * 1e-3) / 1e9} for k, v in per.items()}
+    passes = {k: {"launches_per_step": c // reps, "ms_per_step": ms / reps,
+                  "GBps": b / (ms * 1e-3) / 1e9} for k, (c, ms, b) in per.items()}
     step_bytes = forward_bytes(N)
-    kernel_name = _lib.PASS_KERNELS[_lib.PASS_NAMES.index(dom)]
     # ---- the same for hrc_backward (the recomputed forward, then the reverse):
-    # per pass, kernel time and algorithmic bytes over that time ---------------
-    log("per-pass kernel timing of the backward")
-    bper = {}
+    # per kernel, its time and algorithmic bytes over that time ----------------
+    log("per-kernel timing of the backward")
     breps = max(3, args.steps // 10)
-    for _ in range(breps):
-        for name, n, ms in ctx.hrc_profile_solve(eps, sig, dF):
-            # the backward's traced-levels pass stores all three levels
-            nb = pass_bytes("seed_all" if name == "seed" else name, N, n)
-            tot_ms, tot_b, cnt = bper.get(name, (0.0, 0.0, 0))
-            bper[name] = (tot_ms + ms, tot_b + nb, cnt + 1)
-    backward_passes = {k: {"launches_per_call": v[2] // breps, "ms_per_call": v[0] / breps,
-                           "us_per_launch": v[0] / v[2] * 1e3,
-                           "GBps": v[1] / (v[0] * 1e-3) / 1e9,
-                           "frac_of_hbm_peak": v[1] / (v[0] * 1e-3) / 1e9 / HBM_PEAK_GBPS}
-                       for k, v in bper.items()}
+    bper = kernel_times(backward_launches(N), breps, eps, sig, dF)
+    backward_passes = {k: {"launches_per_call": c // breps, "ms_per_call": ms / breps,
+                           "us_per_launch": ms / c * 1e3,
+                           "GBps": b / (ms * 1e-3) / 1e9,
+                           "frac_of_hbm_peak": b / (ms * 1e-3) / 1e9 / HBM_PEAK_GBPS}
+                       for k, (c, ms, b) in bper.items()}
     # ---- the same forward replayed from a HIP graph (ten solves captured in
     # one graph): the time between the passes is the GPU's drain and ramp at
     # each kernel boundary, which a graph keeps ---------------------------------

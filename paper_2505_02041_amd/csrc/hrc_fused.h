@@ -30,7 +30,7 @@
 // and four down: 76), bound by vector and scalar issue (35 and 40 thousand
 // instructions a CU in 58 thousand cycles); R_6 -> R_4 -> R_2 20.9 us each (two
 // single levels 24, but those need T_3 and T_5 stored), 67 MB, half HBM and half
-// issue.  Forward 217.7 -> 119 us, 64^2 37 -> 24 us (3 launches for 11).  Block
+// issue.  Forward 217.7 -> 118 us, 64^2 37 -> 18 us (3 launches for 11).  Block
 // sizes: the LDS of a top or four-level block (78 and 58 KB) leaves two on a CU,
 // so FP32 blocks of 1024 threads fill its 32 waves (512: 32 and 25.6 us); the
 // 16-bit ones fit three to five (1024: 30.5 and 23.8 us, 512: 28.2 and 20.4), and
@@ -887,7 +887,9 @@ __device__ __forceinline__ void fuse_down_block(const FuseArgs &a, char *lds, in
 // T_n's transmittances from column x0 - 6 on, and two columns of dR_{n+1} more
 // than the block writes.  The transmittances of T_{n+1} and T_{n+2} are rebuilt.
 // Lookups run down the window, at most 4 + 8 rows, so the first 12 rows of a
-// window hold no valid results.
+// window hold no valid results.  1024^2: 22.8 us a pair, 69 MB, for 34 of two single
+// levels; vector and scalar issue (20 and 24 thousand instructions a CU) and the
+// loads' latency share the time (512 threads: 24).
 template <typename TS> struct FuseDr {
     static constexpr int L = kWindow, V = 2, ch = Store<TS>::ch;
     static constexpr int NT = ch == 3 ? 512 : 256, NW = NT / 64;

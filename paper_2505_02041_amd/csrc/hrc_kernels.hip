@@ -1072,8 +1072,6 @@ __device__ __forceinline__ void body_tail(const TailArgs &a, unsigned tile, char
 
 // Transpose of the gather: dR_0[q][x][y] = dF at the image pixel of frame
 // point (x - 1, y), and 0 at x = 0.  Tile = q * tiles^2 + (x tile, y tile).
-constexpr int kGatherAdjLds = 32 * 33 * 4;
-
 __device__ void body_gather_adj(const GatherAdjArgs &a, unsigned tile, char *lds, int tid) {
     float (*ga_tile)[33] = reinterpret_cast<float (*)[33]>(lds);
     const int N = a.N, S = 1 << N;
@@ -1952,8 +1950,8 @@ template <int TILE> struct SeedTileRgb {
     static constexpr int lds = 3 * span * pitch * 16;
 };
 
-// Traced level T_2 of every quadrant (the tail folds T_0 and T_1 itself), and
-// T_0, T_1 as well for the reverse's recomputed forward (a.first = 0).
+// Traced level T_2 of every quadrant (the tail and the reverse's tile kernels
+// fold T_0 and T_1 themselves).
 template <int TILE, typename TS>
 __device__ void body_seed_rgb(const SeedArgs &a, unsigned tile, char *lds, int tid) {
     using G = SeedTileRgb<TILE>;
@@ -1998,11 +1996,7 @@ __device__ void body_seed_rgb(const SeedArgs &a, unsigned tile, char *lds, int t
         }
     }
     __syncthreads();
-    for (int g = 0; g < a.nq; ++g) {
-        if (a.first <= 0) seed_level_rays<TILE, 0, TS, float4>(iv, a, a.q0 + g, g, r0, c0, tid);
-        if (a.first <= 1) seed_level_rays<TILE, 1, TS, float4>(iv, a, a.q0 + g, g, r0, c0, tid);
-        seed_level_rays<TILE, 2, TS, float4>(iv, a, a.q0 + g, g, r0, c0, tid);
-    }
+    for (int g = 0; g < a.nq; ++g) seed_level_rays<TILE, 2, TS, float4>(iv, a, a.q0 + g, g, r0, c0, tid);
     __syncthreads();
 }
 
@@ -2966,10 +2960,6 @@ template <int TILE, int CH> __global__ __launch_bounds__(256) void hrc_tail_adj(
     __shared__ __align__(16) char lds[TailAdjTile<TILE, CH>::lds];
     body_tail_adj<TILE, CH>(p.a.ta, xcd_tile(blockIdx.x, gridDim.x), lds, ltid());
 }
-__global__ __launch_bounds__(256) void hrc_gather_adj(Phase p) {
-    __shared__ __align__(16) char lds[kGatherAdjLds];
-    body_gather_adj(p.a.ga, blockIdx.x, lds, ltid());
-}
 
 template <typename TS, int G>
 __global__ __launch_bounds__((FuseUp<TS, G>::NT)) void hrc_fuse_up(Phase p) {
@@ -3373,7 +3363,6 @@ hipError_t launch_phase(const Phase &p, hipStream_t s, hipEvent_t start, hipEven
             if (p.a.tail.tile == 16) k = p.a.tail.R1 ? hrc_tail<16, true> : hrc_tail<16, false>;
             else k = p.a.tail.R1 ? hrc_tail<32, true> : hrc_tail<32, false>;
             break;
-        case PH_GATHER_ADJ: k = hrc_gather_adj; break;
         case PH_TAIL_ADJ:
             if (p.a.ta.tile == 16) k = p.a.ta.rgb ? hrc_tail_adj<16, 3> : hrc_tail_adj<16, 1>;
             else k = p.a.ta.rgb ? hrc_tail_adj<32, 3> : hrc_tail_adj<32, 1>;
