@@ -57,7 +57,7 @@ def test_fused_levels_match_single_levels(ctx, S):
     ctx.release_workspaces()
 
 
-@pytest.mark.parametrize("S", [16, 32, 64, 128, 256, 512])
+@pytest.mark.parametrize("S", [16, 32, 64, 128, 256, 512, 1024])
 @pytest.mark.parametrize("half", [False, True], ids=["f32", "f16"])
 def test_fused_rgb_matches_channels(ctx, S, half):
     from paper_2505_02041_amd import _lib
