@@ -92,7 +92,7 @@ typedef enum {
 #define HRC_FLAG_HALF_INTERVALS 0x4u
 /* HRC_FLAG_KEEP_PYRAMID (hrc_forward, and the workspace query) and
  * HRC_FLAG_REUSE_PYRAMID (hrc_backward): a reserve space between a forward
- * and its reverse.  The reverse reads the interval pyramid T_0 .. T_(N-1) of
+ * and its reverse.  The reverse reads the interval pyramid T_2 .. T_(N-1) of
  * the four quadrants and the cascade levels R_1 .. R_(N-1); hrc_backward
  * alone recomputes them from emission and sigma_t.  With KEEP the forward
  * computes them as the backward would and leaves them in its workspace, which
@@ -287,7 +287,7 @@ hrc_status hrc_multibounce_backward(hrc_context *ctx, int log2_size, const float
 
 /* Pass kinds reported by hrc_profile_solve. */
 typedef enum {
-    HRC_PASS_SEED = 0,        /* traced levels T_0..T_2 (Section 4.2); the forward stores T_2 only */
+    HRC_PASS_SEED = 0,        /* traced levels T_0..T_2 (Section 4.2); T_2 only is stored */
     HRC_PASS_MERGE_UP = 1,    /* T_n from T_(n-1) (Eq. 18-20) */
     HRC_PASS_MERGE_DOWN = 2,  /* R_n from R_(n+1), T_n, T_(n+1) (Eq. 14-17), down to level 2
                                  (forward) or 1 (the reverse's recomputed forward) */
@@ -308,8 +308,8 @@ typedef enum {
  * and end on `stream`; then synchronises `stream` and reports, per pass in
  * execution order, its kind, level n (-1 when not per level) and kernel
  * duration in milliseconds; a kernel that runs several passes (levels of the
- * merges) reports each with an equal share of its duration.  At most `max_passes` are reported; *count receives the
- * number of passes.  Argument checks as for hrc_forward / hrc_backward, plus
+ * merges) reports each with an equal share of its duration.  At most
+ * `max_passes` are reported; *count receives the number of passes.  Argument checks as for hrc_forward / hrc_backward, plus
  * HRC_ERR_INVALID_ARG for NULL report arrays. */
 hrc_status hrc_profile_solve(hrc_context *ctx, int log2_size,
                              const float *emission, const float *sigma_t, float *fluence,

@@ -22,8 +22,8 @@ Layout make_layout(int N, bool backward, int group, bool half, bool rgb) {
     const size_t SS = L.S * L.S;
     const size_t planes = rgb ? 3 : 1;
     size_t off = 256;  // first 256 bytes: scratch flag for HRC_FLAG_VALIDATE
-    // the forward's tail folds T_0 and T_1 itself (only the reverse stores
-    // them), and the merge down builds what it reads of T_N itself
+    // the tail folds T_0 and T_1 itself (only the persistent kernel's reverse
+    // stores them), and the merge down builds what it reads of T_N itself
     const size_t iv_bytes = rgb    ? (half ? 4 * sizeof(uint16_t) : sizeof(float4))
                             : half ? 2 * sizeof(uint16_t)
                                    : sizeof(float2);

@@ -69,7 +69,7 @@ struct SeedArgs {
     float2 *T0, *T1, *T2;
     size_t e0, e1, e2;  // entries per quadrant of each level
     int N, q0, nq;
-    int tile;           // image tile side: 32 standalone, 16 in the persistent kernel
+    int tile;           // image tile side: 16 up to 512^2 and in the persistent kernel, else 32
     int first;          // first level written: 0, or 2 when the tail folds T_0 and T_1 itself
     int half;           // T levels stored as 16-bit (L, T) pairs (HRC_FLAG_HALF_INTERVALS)
 };
