@@ -207,20 +207,23 @@ __device__ __forceinline__ bool window_inside(int y0, int p, int sb, int S) {
 // far behind it the far column's direction k lies.  yv: the output's grid row
 // plus the rows a column of level m - 1 climbs along the lower edge.  The far
 // lookups run 2k rows up for direction k and 2k + 2 for k + 1, so apart from
-// one base each every LDS offset is an immediate.
+// two bases each every LDS offset is an immediate.  next: the offset of direction
+// k + 1, L, or 0 at the column's last direction (no 2k + 1 there, odd is not used):
+// the row after that one is the next column's first, or at the last column one past
+// the level.  (1024^2 forward 119 us so, 143 with a branch around the three reads.)
 template <typename TS, int V, int L, bool ODD, bool IN>
 __device__ __forceinline__ void fused_up(const TS *nb, int far, int k, const Rows<V> &w, int yv,
                                          typename Store<TS>::C (&even)[V],
-                                         typename Store<TS>::C (&odd)[V]) {
+                                         typename Store<TS>::C (&odd)[V], int next) {
     using C = typename Store<TS>::C;
     const TS *fb = nb + far + 2 * k;
     C n0[V], n1[V], f00[V], f02[V], f10[V];
     ld_row<V>(nb, n0);
     ld_row<V>(fb, f00);  // direction k, 2k rows up
     if constexpr (ODD) {
-        ld_row<V>(nb + L, n1);
+        ld_row<V>(nb + next, n1);
         ld_row<V>(fb + 2, f02);  // direction k, 2k + 2 rows up
-        ld_row<V>(fb + L, f10);  // direction k + 1, 2k rows up
+        ld_row<V>(fb + next, f10);  // direction k + 1, 2k rows up
     }
     const bool in0 = IN || w.in(yv + 2 * k), in1 = IN || w.in(yv + 2 * k + 2);
     if constexpr (!IN) {
@@ -354,8 +357,8 @@ __device__ __forceinline__ float4 load_weight(int n, int ii, const float *envq, 
     }
     return w;
 }
-// Lookups of rows past the valid ones run up to this many rows past an LDS row
-// (and past the last one: the padding of every buffer).
+// Lookups of rows past the valid ones run into the next LDS row, past the last
+// one of the array by at most 16 entries (direction 8 of the fourth level up).
 constexpr int kFusePad = 64;
 
 // Two directions of COLS columns of T_n into LDS, in two halves so that other
@@ -435,7 +438,7 @@ __device__ __forceinline__ void fuse_up_level(const FuseArgs &a, const FuseTile 
         const int y = w.y(X << j);
         C ev[V], od[V];
         fused_up<TS, V, L, true, IN>(src + (2 * X * pdirs + k) * L + w.r, pdirs * L, k, w,
-                                     y + (sb << (j - 1)), ev, od);
+                                     y + (sb << (j - 1)), ev, od, two ? L : 0);
         if constexpr (j < G) {
             TS *d = dst + (X * dirs + 2 * k) * L + w.r;
             st_row<V>(d, ev);
@@ -552,7 +555,7 @@ __device__ __forceinline__ void fuse_top_up(const FuseArgs &a, const FuseTile &t
         constexpr int far = j == 1 ? (1 - (1 << (M - 1))) * 2 * L : pdirs * L;
         C ev[V], od[V];
         fused_up<TS, V, L, true, IN>(top_t<TS, M, j - 1>(lds, 2 * X) + k * L + w.r, far, k, w,
-                                     y + (sb << (j - 1)), ev, od);
+                                     y + (sb << (j - 1)), ev, od, two ? L : 0);
         TS *d = top_t<TS, M, j>(lds, X) + 2 * k * L + w.r;
         st_row<V>(d, ev);
         if (two) st_row<V>(d + L, od);
@@ -771,7 +774,8 @@ __device__ __forceinline__ void fuse_down_levels(const FuseArgs &a, const FuseTi
         if (X > F::c1) break;
         const int far = (int)(t0_col(2 * X + 1) - t0_col(2 * X));
         C ev[V], od[V];
-        fused_up<TS, V, L, true, IN>(t0_col(2 * X) + k * L + w.r, far, k, w, w.y(2 * X - 1) + sb, ev, od);
+        fused_up<TS, V, L, true, IN>(t0_col(2 * X) + k * L + w.r, far, k, w, w.y(2 * X - 1) + sb, ev, od,
+                                     k == 0 ? L : 0);
         TS *d = t1_col(X) + 2 * k * L + w.r;
         st_row<V>(d, ev);
         if (k == 0) st_row<V>(d + L, od);
@@ -800,7 +804,7 @@ __device__ __forceinline__ void fuse_down_levels(const FuseArgs &a, const FuseTi
 #pragma unroll
             for (int up = 0; up < 2; ++up) {
                 fused_up<TS, V, L, false, IN>(t1_col(2 * cc) + (k + up) * L + w.r, 3 * L, k + up, w,
-                                              y + 2 * sb, ed[up], none);
+                                              y + 2 * sb, ed[up], none, 0);
 #pragma unroll
                 for (int j = 0; j < V; ++j) ed[up][j] = stored(ed[up][j], static_cast<const TS *>(nullptr));
             }
