@@ -357,15 +357,17 @@ __device__ __forceinline__ float4 load_weight(int n, int ii, const float *envq, 
     }
     return w;
 }
-// Lookups of rows past the valid ones run into the next LDS row, past the last
-// one of the array by at most 16 entries (direction 8 of the fourth level up).
-constexpr int kFusePad = 64;
+// Entries of padding after a level in LDS: lookups of rows past the valid ones run up
+// to 16 entries past their row (direction 8 of the fourth level up), and behind the
+// last row of a level come rows that other waves are storing, or the array's end.
+constexpr int kFusePad = 16;
 
 // Two directions of COLS columns of T_n into LDS, in two halves so that other
 // loads can be issued between: load() takes the columns first_col .. into
 // registers, store() puts direction ii + d of column i into LDS row
-// 2 slot(i) + d.  No branches (a wave past the last row repeats it), so that
-// every load is in flight before the first wait.  Columns past the grid's last
+// 2 slot(i) + d.  The loads take no branch (a wave past the last row loads it
+// again), so that every one is in flight before the first wait; its store is left
+// out, behind a pin that keeps the load out of that branch.  Columns past the grid's last
 // repeat it (and feed no stored value).
 template <typename TS, int V, int L, int NT, int COLS> struct TnLoad {
     using Raw = typename RawVec<sizeof(TS) * V>::type;
@@ -388,9 +390,13 @@ template <typename TS, int V, int L, int NT, int COLS> struct TnLoad {
         }
     }
     template <typename Slot>
-    __device__ __forceinline__ void store(TS *lds, int wave, int lane, Slot slot) const {
+    __device__ __forceinline__ void store(TS *lds, int wave, int lane, Slot slot) {
 #pragma unroll
         for (int it = 0; it < IT; ++it) {
+            if ((it + 1) * NW > ROWS) {
+                pin_raw(v[it]);
+                if (it * NW + wave >= ROWS) break;
+            }
             const int i = row(it, wave), h = i % H, rd = i / H, d = rd & 1;
             *reinterpret_cast<Raw *>(lds + (slot(rd >> 1) * 2 + d) * L + (h * 64 + lane) * V) = v[it];
         }
@@ -413,7 +419,9 @@ template <typename TS, int G> struct FuseUp {
         for (int j = p; j < G; j += 2) m = rows(j) > m ? rows(j) : m;
         return m;
     }
-    static constexpr int lds = ((region(0) + region(1)) * L + kFusePad) * (int)sizeof(TS);
+    static constexpr int reg1 = region(0) * L + kFusePad;  // first entry of the second region
+    static constexpr int lds = (reg1 + region(1) * L + kFusePad) * (int)sizeof(TS);
+    static_assert((2 << (G - 1)) <= kFusePad, "the last level's lookups");
 };
 
 template <typename TS, int G, int j, bool IN>
@@ -424,7 +432,7 @@ __device__ __forceinline__ void fuse_up_level(const FuseArgs &a, const FuseTile 
     constexpr int V = F::V, L = F::L, H = F::H, NW = F::NW;
     constexpr int dirs = (1 << j) + 1, pdirs = (1 << (j - 1)) + 1, cols = 1 << (G - j);
     const int N = a.N, S = 1 << N, m = a.n + j;
-    TS *reg0 = reinterpret_cast<TS *>(lds), *reg1 = reg0 + F::region(0) * L;
+    TS *reg0 = reinterpret_cast<TS *>(lds), *reg1 = reg0 + F::reg1;
     const TS *src = (j & 1) ? reg0 : reg1;
     TS *dst = (j & 1) ? reg1 : reg0;
     TS *out = reinterpret_cast<TS *>(a.T[j]);
@@ -500,9 +508,9 @@ template <typename TS, int M> struct FuseTop {
     static constexpr int win = L - 2 * ((1 << M) - 1);  // halo: from column 1 to the far edge
     static constexpr int cols(int j) { return (1 << (M - j)) - 1; }
     static constexpr int t_rows(int j) { return cols(j) * ((1 << j) + 1); }
-    static constexpr int t_off(int j) {  // first LDS row of T_{n+j}
+    static constexpr int t_off(int j) {  // first entry of T_{n+j}
         int o = 0;
-        for (int i = 0; i < j; ++i) o += t_rows(i);
+        for (int i = 0; i < j; ++i) o += t_rows(i) * L + kFusePad;
         return o;
     }
     static constexpr int r_rows(int j) { return cols(j) * (1 << j) * ch; }
@@ -511,12 +519,13 @@ template <typename TS, int M> struct FuseTop {
         for (int j = p == 0 ? 2 : 1; j < M; j += 2) m = r_rows(j) > m ? r_rows(j) : m;
         return m;
     }
-    static constexpr int t_bytes = t_off(M) * L * (int)sizeof(TS);
-    static constexpr int r_bytes = (r_region(0) + r_region(1)) * L * 4;
+    static constexpr int t_bytes = t_off(M) * (int)sizeof(TS);
+    static constexpr int r1_at = r_region(0) * L + kFusePad;  // the odd levels' region
+    static constexpr int r_bytes = (r1_at + r_region(1) * L + kFusePad) * 4;
     static constexpr int odd_bytes = (1 << (M - 1)) * 2 * L * (int)sizeof(TS);
     static constexpr bool overlay = t_rows(0) * L * (int)sizeof(TS) - odd_bytes >= r_bytes;
     static constexpr int r_off = overlay ? odd_bytes : t_bytes;
-    static constexpr int w_off = (overlay ? t_bytes : t_bytes + r_bytes) + kFusePad * (int)sizeof(TS);
+    static constexpr int w_off = overlay ? t_bytes : t_bytes + r_bytes;
     static constexpr int lds = w_off + 16 * ((1 << M) - 1);
     // LDS column of T_n's column x: odd columns first
     __device__ __forceinline__ static int slot(int x) {
@@ -524,16 +533,16 @@ template <typename TS, int M> struct FuseTop {
     }
 };
 
-// First LDS row (direction 0) of column x of T_{n+j}; of R_{n+j}.
+// First entry (direction 0, cone 0) of column x of T_{n+j}; of R_{n+j}.
 template <typename TS, int M, int j> __device__ __forceinline__ TS *top_t(char *lds, int x) {
     using F = FuseTop<TS, M>;
     const int c = j == 0 ? F::slot(x) : x - 1;
-    return reinterpret_cast<TS *>(lds) + (F::t_off(j) + c * ((1 << j) + 1)) * F::L;
+    return reinterpret_cast<TS *>(lds) + F::t_off(j) + c * ((1 << j) + 1) * F::L;
 }
 template <typename TS, int M, int j> __device__ __forceinline__ float *top_r(char *lds, int x) {
     using F = FuseTop<TS, M>;
     return reinterpret_cast<float *>(lds + F::r_off) +
-           (((j & 1) ? F::r_region(0) : 0) + (x - 1) * (1 << j) * F::ch) * F::L;
+           ((j & 1) ? F::r1_at : 0) + (x - 1) * (1 << j) * F::ch * F::L;
 }
 
 template <typename TS, int M, int j, bool IN>
@@ -693,13 +702,14 @@ template <typename TS> struct FuseDown {
     static constexpr int c0 = CC + 3, c1 = CC / 2 + 1, c2 = CC / 4 + 1;  // columns per level
     static constexpr int t0_rows = 2 * c0, t1_rows = 3 * c1;
     static constexpr int odd_bytes = (CC / 2) * 2 * L * (int)sizeof(TS);
-    static constexpr int t_bytes = (t0_rows + t1_rows) * L * (int)sizeof(TS);
+    static constexpr int t1_at = t0_rows * L + kFusePad;  // first entry of T_{n+1}
+    static constexpr int t_bytes = (t1_at + t1_rows * L + kFusePad) * (int)sizeof(TS);
     static constexpr int r2_bytes = c2 * 4 * ch * L * 4, r1_bytes = c1 * 2 * ch * L * 4;
     static constexpr bool overlay =
         t0_rows * L * (int)sizeof(TS) - odd_bytes >= r1_bytes + r2_bytes;
     static constexpr int r1_off = overlay ? odd_bytes : t_bytes, r2_off = r1_off + r1_bytes;
     static constexpr int w_off =
-        t_bytes + (overlay ? 0 : r1_bytes + r2_bytes) + kFusePad * (int)sizeof(TS);
+        t_bytes + (overlay ? 0 : r1_bytes + r2_bytes + kFusePad * 4);
     static constexpr int lds = w_off + 16 * 3;
     // LDS column of T_n's column x0 + i: the odd ones below CC first, then the
     // rest in order
@@ -734,9 +744,13 @@ template <typename TS> struct R2Load {
                  (unsigned)w.y(4 * c - 1)));
         }
     }
-    __device__ __forceinline__ void store(float *r2, int wave, int lane) const {
+    __device__ __forceinline__ void store(float *r2, int wave, int lane) {
 #pragma unroll
         for (int it = 0; it < IT; ++it) {
+            if ((it + 1) * F::NW > ROWS) {
+                pin_raw(v[it]);
+                if (it * F::NW + wave >= ROWS) break;
+            }
             const int i = row(it, wave);
             *reinterpret_cast<Raw *>(r2 + (i / H) * F::L + ((i % H) * 64 + lane) * V) = v[it];
         }
@@ -745,14 +759,14 @@ template <typename TS> struct R2Load {
 
 template <typename TS, bool IN>
 __device__ __forceinline__ void fuse_down_levels(const FuseArgs &a, const FuseTile &t, char *lds,
-                                                 const R2Load<TS> &rl, int own, int sb, int tid) {
+                                                 R2Load<TS> &rl, int own, int sb, int tid) {
     using F = FuseDown<TS>;
     using C = typename Store<TS>::C;
     constexpr int V = F::V, L = F::L, H = F::H, NW = F::NW, CH = F::ch, CC = F::CC;
     const int N = a.N, S = 1 << N, n = a.n, x0 = t.x * CC, cols = S >> n;
     const size_t plane = (size_t)a.nq << (2 * N);
     const int wave = __builtin_amdgcn_readfirstlane(tid >> 6), lane = tid & 63;
-    TS *t0 = reinterpret_cast<TS *>(lds), *t1 = t0 + F::t0_rows * L;
+    TS *t0 = reinterpret_cast<TS *>(lds), *t1 = t0 + F::t1_at;
     float *r2 = reinterpret_cast<float *>(lds + F::r2_off);
     float *r1 = reinterpret_cast<float *>(lds + F::r1_off);
     const float4 *wl = reinterpret_cast<const float4 *>(lds + F::w_off);
@@ -902,7 +916,7 @@ template <typename TS> struct FuseDr {
     static constexpr int pad = 16;  // floats before the first row
     static constexpr int d0_off = pad, t0_off = d0_off + d0_cols * ch * L, t1_off = t0_off + t0_cols * 2 * L;
     static constexpr int d1_off = t1_off + t1_cols * 3 * L;
-    static constexpr int lds = (d1_off + d1_cols * 2 * ch * L + kFusePad) * 4;
+    static constexpr int lds = (d1_off + d1_cols * 2 * ch * L) * 4;
 };
 
 __device__ __forceinline__ float stored_t(float v, const float2 *) { return v; }
@@ -982,14 +996,21 @@ __device__ __forceinline__ void fuse_dr_block(const FuseArgs &a, char *lds, int 
         }
 #pragma unroll
         for (int it = 0; it < DI; ++it) {
-            int i = it * NW + wave;
-            i = i < DR ? i : DR - 1;
+            const int i = it * NW + wave;
+            if ((it + 1) * NW > DR) {
+                pin_raw(dv[it]);
+                if (i >= DR) break;
+            }
             *reinterpret_cast<typename RawVec<8>::type *>(d0 + i * L + w.r) = dv[it];
         }
 #pragma unroll
         for (int it = 0; it < TI; ++it) {
-            int i = it * NW + wave;
-            i = i < TR ? i : TR - 1;
+            const int i = it * NW + wave;
+            if ((it + 1) * NW > TR) {
+                pin_raw(tv[it][0]);
+                if constexpr (sizeof(TS) * V == 32) pin_raw(tv[it][1]);
+                if (i >= TR) break;
+            }
             TS e[V];
             __builtin_memcpy(e, tv[it], sizeof(e));
             *reinterpret_cast<float2 *>(t0 + i * L + w.r) = make_float2(raw_t(e[0]), raw_t(e[1]));

@@ -173,6 +173,7 @@ __device__ __forceinline__ _Float16 to_half(float v) {
 __device__ __forceinline__ void pin(float &v) { asm volatile("" : "+v"(v)); }
 __device__ __forceinline__ void pin(float2 &v) { pin(v.x); pin(v.y); }
 __device__ __forceinline__ void pin(float4 &v) { pin(v.x); pin(v.y); pin(v.z); pin(v.w); }
+template <typename Raw> __device__ __forceinline__ void pin_raw(Raw &v) { asm volatile("" : "+v"(v)); }
 
 __device__ __forceinline__ float4 ld_pair(const half2_t *p) {
     const half4_t v = *reinterpret_cast<const half4_t *>(p);

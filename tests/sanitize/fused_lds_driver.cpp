@@ -59,6 +59,7 @@ static _Float16 to_half(float v) { return (_Float16)v; }
 static void pin(float &) {}
 static void pin(float2 &) {}
 static void pin(float4 &) {}
+template <typename Raw> void pin_raw(Raw &) {}
 static float4 ld_pair(const half2_t *p) {
     const half4_t v = *reinterpret_cast<const half4_t *>(p);
     return make_float4((float)v.x, (float)v.y, (float)v.z, (float)v.w);

@@ -6,6 +6,10 @@ array and every buffer at its exact size.
 Bounds: under AddressSanitizer, every tile of small grids.  The parametrised types
 and levels are those a launch can choose, each with all levels stored and with the
 last alone, on grids with one window and with several.
+
+Races: under ThreadSanitizer, one block of each with its threads as threads and its
+barriers as barriers.  Also a read whose value nothing uses, or a second store of
+the same value, counts.
 """
 import os
 import subprocess
@@ -34,3 +38,7 @@ def _run(tmp_path, sanitizer, define):
 
 def test_every_access_in_bounds(tmp_path):
     _run(tmp_path, "address", "-DBOUNDS")
+
+
+def test_no_unsynchronised_access(tmp_path):
+    _run(tmp_path, "thread", "-DRACES")
