@@ -871,13 +871,14 @@ __device__ __forceinline__ float r2_at(const float *R2, int ro, int jj, int y, i
 // tiles) 11.8 -> 10.8 us, 1024^2 21.2 -> 20.7.  What remains is the rays' and cones'
 // arithmetic (35 thousand vector instructions a CU in 42 thousand cycles at 1024^2).
 // The persistent batch keeps one body for the four (its kernels are short of
-// registers).
+// registers); N is an argument because the arguments of its passes lie in memory and
+// were read again for every quadrant (its forward batches 1.0-1.6% faster so).
 template <int TILE, bool KEEP, int Q>
-__device__ __forceinline__ void tail_quadrant(const TailArgs &a, int g, int r0, int c0,
+__device__ __forceinline__ void tail_quadrant(const TailArgs &a, int N, int g, int r0, int c0,
                                               const float2 *iv, float *r1, float *acc, int tid) {
     using G = TailTile<TILE>;
     constexpr int H = G::halo, P = G::pitch, RR = G::r1rows, AP = G::acc_pitch;
-    const int N = a.N, S = 1 << N, q = Q < 0 ? a.q0 + g : Q;
+    const int S = 1 << N, q = Q < 0 ? a.q0 + g : Q;
     // (else the offsets of all four quadrants are hoisted out of the loop: 256 registers)
     if constexpr (Q >= 0) asm volatile("" : "+v"(tid));
     const float *R2 = a.R2 + (size_t)g * S * S;
@@ -1049,14 +1050,14 @@ __device__ __forceinline__ void body_tail(const TailArgs &a, unsigned tile, char
     }
     for (int g = 0; g < a.nq; ++g) {
         if constexpr (!QUADS) {
-            tail_quadrant<TILE, KEEP, -1>(a, g, r0, c0, iv, r1, acc, tid);
+            tail_quadrant<TILE, KEEP, -1>(a, N, g, r0, c0, iv, r1, acc, tid);
             continue;
         }
         switch (a.q0 + g) {
-            case 0: tail_quadrant<TILE, KEEP, 0>(a, g, r0, c0, iv, r1, acc, tid); break;
-            case 1: tail_quadrant<TILE, KEEP, 1>(a, g, r0, c0, iv, r1, acc, tid); break;
-            case 2: tail_quadrant<TILE, KEEP, 2>(a, g, r0, c0, iv, r1, acc, tid); break;
-            default: tail_quadrant<TILE, KEEP, 3>(a, g, r0, c0, iv, r1, acc, tid); break;
+            case 0: tail_quadrant<TILE, KEEP, 0>(a, N, g, r0, c0, iv, r1, acc, tid); break;
+            case 1: tail_quadrant<TILE, KEEP, 1>(a, N, g, r0, c0, iv, r1, acc, tid); break;
+            case 2: tail_quadrant<TILE, KEEP, 2>(a, N, g, r0, c0, iv, r1, acc, tid); break;
+            default: tail_quadrant<TILE, KEEP, 3>(a, N, g, r0, c0, iv, r1, acc, tid); break;
         }
     }
     __syncthreads();
