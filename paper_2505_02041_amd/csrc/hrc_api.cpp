@@ -148,9 +148,6 @@ static int pick_u(const int *U, int kind) { return U ? (U[kind] > 0 ? U[kind] : 
 // forward 2-7%, the RGB forward 4% and the reverse 3-9% faster at 1024^2 ..
 // 4096^2; the same results, since only the order of the tiles changes.
 static int tile_order(int N, int kind) {
-    if (kind == PH_FUSE_UP || kind == PH_FUSE_TOP || kind == PH_FUSE_DOWN ||
-        kind == PH_FUSE_DR)
-        return 0;
     if (N < 10) return 0;
     switch (kind) {
         case PH_UP:

@@ -355,10 +355,11 @@ __device__ __forceinline__ void seed_level_rays(const I *iv, const SeedArgs &a, 
     }
 }
 
-// TILE x TILE image pixels per work tile (32 for the standalone kernel, 16
+// TILE x TILE image pixels per work tile (32 or 16 for the standalone kernels, 16
 // inside the persistent kernel, whose one LDS buffer serves every pass); the
-// per-ray arithmetic is the same for both.
-template <int TILE, typename TS>
+// per-ray arithmetic is the same for all.  LOW: the levels from a.first on (the
+// persistent kernel's reverse reads T_0 and T_1), else T_2 alone.
+template <int TILE, typename TS, bool LOW>
 __device__ __forceinline__ void body_seed(const SeedArgs &a, unsigned tile, char *lds, int tid) {
     using G = SeedTile<TILE>;
     float2 *iv = reinterpret_cast<float2 *>(lds);
@@ -399,8 +400,8 @@ __device__ __forceinline__ void body_seed(const SeedArgs &a, unsigned tile, char
     }
     __syncthreads();
     for (int g = 0; g < a.nq; ++g) {
-        if (a.first <= 0) seed_level_rays<TILE, 0, TS>(iv, a, a.q0 + g, g, r0, c0, tid);
-        if (a.first <= 1) seed_level_rays<TILE, 1, TS>(iv, a, a.q0 + g, g, r0, c0, tid);
+        if (LOW && a.first <= 0) seed_level_rays<TILE, 0, TS>(iv, a, a.q0 + g, g, r0, c0, tid);
+        if (LOW && a.first <= 1) seed_level_rays<TILE, 1, TS>(iv, a, a.q0 + g, g, r0, c0, tid);
         seed_level_rays<TILE, 2, TS>(iv, a, a.q0 + g, g, r0, c0, tid);
     }
     __syncthreads();
@@ -1342,7 +1343,7 @@ __device__ void body_merge_down_adj(const DownAdjArgs &a, unsigned tile, int U, 
             const float *grow = a.dR + (qS + ((unsigned)((x << n) | ii) << N));
             const TS *trow = reinterpret_cast<const TS *>(a.Tn) +
                              ((unsigned)q * (unsigned)a.en + ((unsigned)(x * ((1 << n) + 1) + e) << N));
-            if (n > 0) {
+            if (sizeof(TS) == sizeof(half2_t) || n > 0) {  // 16-bit levels: n >= 2
                 const bool in = (unsigned)y < (unsigned)S;
                 const int yc = in ? y : 0;
                 const float2 gv = *reinterpret_cast<const float2 *>(grow + yc);
@@ -2443,31 +2444,19 @@ __device__ void body_merge_down_adj_rgb(const DownAdjArgs &a, unsigned tile, int
         if (c >= 1) {
             // odd column 2c-1 (far end of Eq. 14) at row y = y' - (2e - 2^n)
             const int e = ii + up, x = 2 * c - 1;
-            const int y = yp - (2 * e - (1 << n));  // odd when n = 0
+            const int y = yp - (2 * e - (1 << n));  // even: n >= 2
             const size_t grow = ((size_t)((x << n) | ii)) * S;
             const TS *trow = reinterpret_cast<const TS *>(a.Tn) + q * a.en +
                              ((size_t)x * ((1 << n) + 1) + e) * S;
-            if (n > 0) {
-                const bool in = (unsigned)y < (unsigned)S;
-                const int yc = in ? y : 0;
-                const float4 ta = ld4(trow + yc), tb = ld4(trow + yc + 1);
+            const bool in = (unsigned)y < (unsigned)S;
+            const int yc = in ? y : 0;
+            const float4 ta = ld4(trow + yc), tb = ld4(trow + yc + 1);
 #pragma unroll
-                for (int ch = 0; ch < 3; ++ch) {
-                    const float2 gv = *reinterpret_cast<const float2 *>(dRq + ch * plane + grow + yc);
-                    g[ch] = in ? gv : make_float2(0.f, 0.f);
-                }
-                t = in ? make_float2(ta.w, tb.w) : make_float2(0.f, 0.f);
-            } else {
-                const bool in0 = (unsigned)y < (unsigned)S, in1 = (unsigned)(y + 1) < (unsigned)S;
-                const int y0 = in0 ? y : 0, y1 = in1 ? y + 1 : 0;
-                const float ta = ld4(trow + y0).w, tb = ld4(trow + y1).w;
-#pragma unroll
-                for (int ch = 0; ch < 3; ++ch) {
-                    const float ga = dRq[ch * plane + grow + y0], gb = dRq[ch * plane + grow + y1];
-                    g[ch] = make_float2(in0 ? ga : 0.f, in1 ? gb : 0.f);
-                }
-                t = make_float2(in0 ? ta : 0.f, in1 ? tb : 0.f);
+            for (int ch = 0; ch < 3; ++ch) {
+                const float2 gv = *reinterpret_cast<const float2 *>(dRq + ch * plane + grow + yc);
+                g[ch] = in ? gv : make_float2(0.f, 0.f);
             }
+            t = in ? make_float2(ta.w, tb.w) : make_float2(0.f, 0.f);
             // even column 2c-2 (far end of Eq. 17) at row y' - (2 e2 - 2^(n+1))
             // (none from column 0, c = 1: as body_merge_down_adj)
             const int e2 = 2 * ii + 2 * up, x2 = 2 * c - 2;
@@ -2859,7 +2848,7 @@ __device__ __forceinline__ void run_phase(const Phase &p, unsigned tile, char *l
     __builtin_assume(t < 256u);
     const int tid = (int)t;
     switch (p.kind) {
-        case PH_SEED: body_seed<16, float2>(p.a.seed, tile, lds, tid); break;  // planner sets tile 16
+        case PH_SEED: body_seed<16, float2, true>(p.a.seed, tile, lds, tid); break;  // planner sets tile 16
         case PH_UP: body_merge_up<float2>(p.a.up, tile, p.U, tid); break;
         case PH_DOWN: body_merge_down<float2>(p.a.down, tile, p.U, tid); break;
         case PH_TAIL: body_tail<16, false, false>(p.a.tail, tile, lds, tid); break;  // planner sets tile 16
@@ -2894,15 +2883,15 @@ HRC_ELEMENTWISE_KERNEL(hrc_interval_adj_f16, body_dT<half2_t>, dt)
 
 __global__ __launch_bounds__(256) void hrc_seed(Phase p) {
     __shared__ __align__(16) char lds[SeedTile<32>::lds];
-    body_seed<32, float2>(p.a.seed, xcd_tile(blockIdx.x, gridDim.x), lds, ltid());
+    body_seed<32, float2, false>(p.a.seed, xcd_tile(blockIdx.x, gridDim.x), lds, ltid());
 }
 template <typename TS> __global__ __launch_bounds__(256) void hrc_seed_16(Phase p) {
     __shared__ __align__(16) char lds[SeedTile<16>::lds];
-    body_seed<16, TS>(p.a.seed, xcd_tile(blockIdx.x, gridDim.x), lds, ltid());
+    body_seed<16, TS, false>(p.a.seed, xcd_tile(blockIdx.x, gridDim.x), lds, ltid());
 }
 __global__ __launch_bounds__(256) void hrc_seed_f16(Phase p) {
     __shared__ __align__(16) char lds[SeedTile<32>::lds];
-    body_seed<32, half2_t>(p.a.seed, xcd_tile(blockIdx.x, gridDim.x), lds, ltid());
+    body_seed<32, half2_t, false>(p.a.seed, xcd_tile(blockIdx.x, gridDim.x), lds, ltid());
 }
 __global__ __launch_bounds__(256) void hrc_seed_adj(Phase p) {
     __shared__ __align__(16) char lds[kSeedAdjLds];
