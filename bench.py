@@ -43,19 +43,27 @@ def parse():
     return ap.parse_args()
 
 
+# What determines a kernel's HBM bytes: its code and helpers, its grid and window,
+# and the levels the solve gives it.
+TRAFFIC_SOURCES = tuple("paper_2505_02041_amd/csrc/" + f for f in (
+    "hrc_fused.h", "hrc_kernels.hip", "hrc_api.cpp", "hrc_internal.h"))
+
+
+def source_hashes() -> dict:
+    import hashlib
+    return {s: hashlib.sha256(open(os.path.join(ROOT, s), "rb").read()).hexdigest()
+            for s in TRAFFIC_SOURCES}
+
+
 def measured_traffic(kernel: str):
     """HBM bytes per launch of `kernel` from the committed FETCH_SIZE/WRITE_SIZE
     profile (scaled by the plain-copy calibration), or None when there is no
-    such profile of it or the kernel source has changed since it was taken."""
-    import hashlib
+    such profile of it or one of TRAFFIC_SOURCES has changed since it was taken."""
     path = os.path.join(ROOT, "profiles", "hrc_forward_1024_traffic.json")
     if not os.path.exists(path):
         return None
     rec = json.load(open(path))
-    src = os.path.join(ROOT, rec["source"])
-    if rec["kernel"] != kernel or not os.path.exists(src):
-        return None
-    if hashlib.sha256(open(src, "rb").read()).hexdigest() != rec["source_sha256"]:
+    if rec["kernel"] != kernel or rec.get("sources_sha256") != source_hashes():
         return None
     return rec["traffic_bytes_per_launch"]
 
