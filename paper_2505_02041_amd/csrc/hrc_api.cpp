@@ -256,10 +256,15 @@ static int build_fused_merges(const Ws &w, const SolveBuffers &b, bool keep, boo
 }
 
 // Image tile of the traced levels, the tail and its adjoint.  Up to 512^2 the
-// larger tile leaves CUs idle (256 blocks of it at 512^2): 16 takes 7.7, 13.2 and
-// 8.3 us there against 8.3, 18.3 and 10.1 (64^2: 5.1 and 9.1 against 5.8 and
-// 14.1); from 1024^2 on its relatively larger halo costs more: 16.2, 32.6 and 22.4
-// us against 12.0, 21.2 and 15.9 there.
+// larger tile leaves CUs idle (256 blocks of it at 512^2); from 1024^2 on the
+// smaller one's relatively larger halo costs more.  us with 16 / with 32 (tail: the
+// one that keeps R_1):
+//            64^2       256^2      512^2      1024^2     2048^2     4096^2
+//   traced   5.4/6.1    6.3/7.6    8.1/8.5   17.1/13.3  59.5/48.2   253/193
+//   tail     9.9/15.8  10.3/18.0  12.2/18.9  37.6/26.5   136/102    540/422
+//   adjoint  5.3/7.7    6.1/9.1    8.5/10.8  22.6/16.9  90.3/59.2   381/248
+//   RGB adj. 7.1/11.8   9.3/14.2  13.5/17.0  54.0/40.0   259/166
+// (RGB: the adjoint alone; its traced levels and tail take 16 at every size.)
 static int tail_tile(int N) { return N <= 9 ? 16 : 32; }
 
 // Two levels of the merge-down adjoint in one kernel: (T_n, dR_n) -> dR_{n+1},

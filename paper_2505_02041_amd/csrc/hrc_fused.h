@@ -25,12 +25,12 @@
 // Column 0 of a level is read by nothing but column 0 of the levels below,
 // and the gather never reads that: the top and the down kernels leave it out.
 //
-// Measured at 1024^2 (FP32, four quadrants, per forward): T_2 -> T_4, T_6 23.2 us
-// (four single levels 40), 107 MB at 4.6 TB/s; T_6 -> R_6 28.5 us (three levels up
+// Measured at 1024^2 (FP32, four quadrants, per forward): T_2 -> T_4, T_6 23.7 us
+// (four single levels 40), 107 MB at 4.5 TB/s; T_6 -> R_6 29.2 us (three levels up
 // and four down: 76), bound by vector and scalar issue (35 and 40 thousand
-// instructions a CU in 58 thousand cycles); R_6 -> R_4 -> R_2 20.9 us each (two
+// instructions a CU in 58 thousand cycles); R_6 -> R_4 -> R_2 21.2 us each (two
 // single levels 24, but those need T_3 and T_5 stored), 67 MB, half HBM and half
-// issue.  Forward 217.7 -> 118 us, 64^2 37 -> 18 us (3 launches for 11).  Block
+// issue.  Forward 217.7 -> 119 us, 64^2 37 -> 18 us (3 launches for 11).  Block
 // sizes: the LDS of a top or four-level block (78 and 58 KB) leaves two on a CU,
 // so FP32 blocks of 1024 threads fill its 32 waves (512: 32 and 25.6 us); the
 // 16-bit ones fit three to five (1024: 30.5 and 23.8 us, 512: 28.2 and 20.4), and
@@ -776,7 +776,7 @@ __device__ __forceinline__ void fuse_down_levels(const FuseArgs &a, const FuseTi
     auto r1_col = [&](int i) { return r1 + (i - 1) * 2 * CH * L; };
     // A wave's items at the levels with two cones: one row part h and cone k, and
     // every DX-th column from xw; the unrolled loops then address by immediates and a
-    // column's parity is the wave's (22.3 -> 20.9 us a pair).
+    // column's parity is the wave's (22.3 -> 20.9 us a pair, 21.2 with next).
     constexpr int DX = NW / (2 * H), IX = (F::c1 + DX - 1) / DX;
     static_assert(NW % (2 * H) == 0, "waves");
     const int h = wave % H, k = wave / H & 1, xw = 1 + wave / (2 * H);
@@ -905,9 +905,12 @@ __device__ __forceinline__ void fuse_down_block(const FuseArgs &a, char *lds, in
 // T_n's transmittances from column x0 - 6 on, and two columns of dR_{n+1} more
 // than the block writes.  The transmittances of T_{n+1} and T_{n+2} are rebuilt.
 // Lookups run down the window, at most 4 + 8 rows, so the first 12 rows of a
-// window hold no valid results.  1024^2: 22.8 us a pair, 69 MB, for 34 of two single
-// levels; vector and scalar issue (20 and 24 thousand instructions a CU) and the
-// loads' latency share the time (512 threads: 24).
+// window hold no valid results.  1024^2: 21 to 26 us a pair (24 on average), 90-93 MB
+// from and to HBM (the levels hold 67-71; 13 columns of dR_n are loaded for 8), for
+// 34 us of two single levels; vector and scalar issue (20 and 24 thousand
+// instructions a CU) and the loads' latency share the time (512 threads: 24).
+// Without the second store of a repeated row a 1024^2 forward and reverse takes 604
+// us for 600, in RGB 1530 for 1544.
 template <typename TS> struct FuseDr {
     static constexpr int L = kWindow, V = 2, ch = Store<TS>::ch;
     static constexpr int NT = ch == 3 ? 512 : 256, NW = NT / 64;

@@ -99,7 +99,7 @@ struct TailArgs {
     int N, q0, nq;
     int accumulate;          // add to out (the groups after the first) instead of storing
     const float *env;        // environment table (nullable)
-    int tile;                // image tile side: 32 standalone, 16 in the persistent kernel
+    int tile;                // image tile side: 16 up to 512^2, in RGB and in the persistent kernel, else 32
     float *R1 = nullptr;     // R_1 as well, for the reverse (nullable; then out may be NULL)
 };
 // The adjoint of the gather and of the merge down of levels 0 and 1: dR_0, dR_1
